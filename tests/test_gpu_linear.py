@@ -84,3 +84,50 @@ def test_linear_rejects_unsupported_shapes(dev):
     empty = torch.zeros((0, 64), dtype=torch.bfloat16, device=dev)
     D.dlfp_linear_bf16(empty, torch.zeros((128, 64), dtype=torch.bfloat16, device=dev),
                        torch.zeros((0, 128), dtype=torch.float32, device=dev))
+
+
+# Both sides of every change of kernel or tile, token counts just past and just short
+# of a tile, and K shorter than the stages and the wavefronts that split it.
+EDGES = [(1, 128, 64), (31, 256, 64), (256, 1024, 128), (257, 1024, 64), (33, 6144, 64),
+         (65, 6144, 1024), (513, 1024, 1024), (513, 1024, 64), (129, 6144, 1024),
+         (2049, 1024, 64), (321, 6144, 64), (641, 6144, 64), (2049, 2048, 192),
+         (1665, 6144, 64), (4097, 2048, 192), (673, 384, 192)]
+
+
+@pytest.mark.parametrize("m,n,k", EDGES)
+def test_linear_dispatch_edges(dev, m, n, k):
+    """fp32 output, bf16 output in 16-byte stores and bf16 output whose rows allow only
+    8-byte ones, in a buffer whose other values stay as they were.  Same bars as above
+    (k <= 1024 here)."""
+    g = torch.Generator(device=dev)
+    g.manual_seed(m + 3 * n + 5 * k)
+    x = torch.empty((m, k), dtype=torch.bfloat16, device=dev).normal_(generator=g)
+    w = (torch.empty((n, k), dtype=torch.float32, device=dev).normal_(generator=g)
+         / math.sqrt(k)).to(torch.bfloat16)
+    want = ol.linear(_bits64(x), _bits64(w))
+    for dtype, left, right in ((torch.float32, 4, 4), (torch.bfloat16, 8, 0),
+                               (torch.bfloat16, 4, 8)):
+        big = torch.full((m, left + n + right), 7.0, dtype=dtype, device=dev)
+        D.dlfp_linear_bf16(x, w, big[:, left:left + n])
+        torch.cuda.synchronize()
+        got = big.double().cpu().numpy()
+        assert (got[:, :left] == 7.0).all() and (got[:, left + n:] == 7.0).all()
+        half_step = 0.0 if dtype == torch.float32 else 2.0 ** -8
+        assert np.all(np.abs(got[:, left:left + n] - want) <= np.abs(want) * half_step + 5e-4)
+
+
+def test_linear_far_rows(dev):
+    """Rows 2^22 elements and more apart (64-bit row offsets)."""
+    g = torch.Generator(device=dev)
+    g.manual_seed(3)
+    m, n, k, ldx = 67, 256, 192, (1 << 22) + 8
+    buf = torch.empty(((m - 1) * ldx + k,), dtype=torch.bfloat16, device=dev)
+    x = buf.as_strided((m, k), (ldx, 1))
+    x.normal_(generator=g)
+    w = (torch.empty((n, k), dtype=torch.float32, device=dev).normal_(generator=g)
+         / math.sqrt(k)).to(torch.bfloat16)
+    out = torch.full((m, n), float("nan"), dtype=torch.float32, device=dev)
+    D.dlfp_linear_bf16(x, w, out)
+    torch.cuda.synchronize()
+    want = ol.linear(_bits64(x.contiguous()), _bits64(w))
+    assert np.abs(out.cpu().numpy() - want).max() <= 5e-4
