@@ -125,20 +125,24 @@ typedef struct {
  * split of at least 1024 keys keeping them at most one per compute unit, come
  * within 1/16 of that count (32 rows when none does); a prefill share alone
  * takes 128-row tiles and the split (a multiple of 64 keys, at least 1024)
- * that minimises an estimate of the launch time.  The decode split is either
- * sqrt(256 W / F) keys for W decode keys over the F wavefronts of the
+ * that minimises an estimate of the launch time.  Without a prefill share a
+ * decode unit is the work of a workgroup, and the decode split is the one in
+ * equal parts (of at least 192 keys) that minimises an estimate of the launch
+ * time.  Beside a prefill share a decode unit is a wavefront's, and the split
+ * is either sqrt(256 W / F) keys for W decode keys over the F wavefronts of the
  * workgroup slots the prefill units leave (several queue rounds), or the
  * split that fits one round and best evens the decode workgroups over the
- * CUs, whichever an estimate of the launch time favours; a range longer than
- * its split is cut into equal parts, the last of them cut again into a half
- * and two quarters when the decode queue runs one to six rounds.  Grid
+ * CUs, whichever an estimate of the launch time favours.  A range longer than
+ * its split is cut into equal parts; the last of them is cut again into a half
+ * and two quarters when the decode queue runs one to six rounds, or workgroup
+ * units of 2048 keys and more one to eight.  Grid
  * layout: when a launch has decode
  * units and more prefill units than compute units, one prefill unit per
  * compute unit leads the grid, then the decode workgroups (up to one per
  * compute unit), then the other prefill units, so that the memory-bound decode
  * share runs beside the matrix-core-bound prefill share from the start instead
- * of after it.  Decode page depth: two pages in flight in a launch without
- * prefill units, one beside them. */
+ * of after it.  Decode page depth of a wavefront's unit: one page in flight;
+ * a launch without prefill units reports two. */
 typedef struct {
   int32_t decode_split_tokens;   /* keys per decode unit; 0 = auto, else a multiple of 16,
                                     at most DLFP_MAX_DECODE_UNIT_KEYS */
@@ -153,7 +157,8 @@ typedef struct {
                                     prefill units placed before the first decode workgroups
                                     (the rest follow them); 0 = auto, -1 = all of them */
   int32_t decode_pages_in_flight;/* pages a decode wavefront keeps in flight beside its
-                                    current one: 0 = auto, 1 or 2 */
+                                    current one: 0 = auto, 1 or 2 (no effect on
+                                    workgroup units) */
 } dlfp_tuning;
 
 /* 256 compute units x 8 resident wavefronts (two 256-thread workgroups per CU). */

@@ -4,7 +4,8 @@
 // the chunk) of Eq. 1, Sec. 2.1, served by one grid.
 //
 // Grid: the work list's prefill units first, one 256-thread workgroup each,
-// then decode units, four per workgroup (one per wavefront).
+// then decode units, four per workgroup (one per wavefront); a launch without
+// prefill units gives each decode unit a workgroup.
 //
 // Prefill unit = (sequence, KV head, tile of 128 query rows, key split).
 // Rows are the tile's tokens x the g query heads sharing the KV head, so each
@@ -21,14 +22,9 @@
 // (one barrier per tile), with XOR swizzles that keep the 16 lanes of each
 // LDS access phase on distinct banks.
 //
-// Decode unit = (sequence, KV head, key split), one wavefront.  Memory-bound:
-// each 16-token page of K and V (8 KiB) is fetched with fully coalesced,
-// non-temporal 16-byte loads one page ahead, staged in the wave's LDS slice,
-// and consumed by VALU bf16 dot products (v_dot2 with fp32 accumulation; with
-// grouped heads, g >= 2, by 16x16 MFMA instead).  Eight lanes share a key (16
-// dims each) and sum their partial dot products with DPP; the per-head row
-// max uses DPP and wavefront shuffles; probabilities are handed to the PV
-// lanes through LDS, and each lane owns two output dims.
+// Decode unit = (sequence, KV head, key split).  Memory-bound: pages of K and V
+// reach LDS by fully coalesced, non-temporal 16-byte copies while earlier ones
+// are consumed by 16x16 matrix products whose columns are the grouped heads.
 //
 // Split-K: a unit whose rows are split over several key ranges writes
 // (unnormalised O, running max, running sum) to its workspace slot, releases,
@@ -72,18 +68,19 @@ constexpr int THREADS = 256;
 constexpr int PRE_PTAB = DLFP_MAX_PREFILL_UNIT_KEYS / PAGE;  // block ids of one prefill unit
 constexpr int PRE_LDS = 4 * KV_TILE * D * 2 + PRE_PTAB * 4;  // 64 KiB of K/V tiles + 8 KiB
 constexpr int DEC_PTAB = DLFP_MAX_DECODE_UNIT_KEYS / PAGE;   // block ids of one decode unit
-// Per decode wave: two slots of (K page, V page), probability buffer, block
-// ids, and (for g = 8) the query of the group.
-constexpr int DEC_Q_LDS = 8 * D * 2;
+// Per decode wavefront: two slots of (K page, V page), block ids.
 constexpr int DEC_PAGE_SLOT = 2 * PAGE_ELEMS * 2;  // K and V page, 8 KiB
-constexpr int DEC_WAVE_LDS = 2 * DEC_PAGE_SLOT + 16 * 16 * 2 + DEC_PTAB * 4 + DEC_Q_LDS;
+constexpr int DEC_WAVE_LDS = 2 * DEC_PAGE_SLOT + DEC_PTAB * 4;
+// Per wavefront of a wide decode unit: a key slot and a value slot of two pages
+// each, ids of its pages.
+constexpr int WIDE_SLOT = 2 * PAGE_ELEMS * 2;
+constexpr int WIDE_WAVE_LDS = 2 * WIDE_SLOT + DEC_PTAB;  // a quarter of a unit's pages, 4 bytes each
 constexpr int LDS_BYTES = PRE_LDS > 4 * DEC_WAVE_LDS ? PRE_LDS : 4 * DEC_WAVE_LDS;
 // Two workgroups per CU (160 KiB of LDS).
 static_assert(2 * (LDS_BYTES + 16) <= 160 * 1024, "two workgroups must share a CU");
 constexpr float NEG_BIG = -1.0e30f;
 constexpr float LOG2E = 1.4426950408889634f;
 
-static_assert(4 * DEC_WAVE_LDS <= LDS_BYTES, "decode slices must fit the shared buffer");
 
 struct Args {
   const int32_t* work;
@@ -129,16 +126,6 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
 }
 
 __device__ __forceinline__ float fexp2(float x) { return __builtin_amdgcn_exp2f(x); }
-
-template <int CTRL>
-__device__ __forceinline__ float dpp(float x) {
-  return __builtin_bit_cast(
-      float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, 0xF, 0xF, false));
-}
-constexpr int DPP_XOR1 = 0xB1;         // quad_perm [1,0,3,2]
-constexpr int DPP_XOR2 = 0x4E;         // quad_perm [2,3,0,1]
-constexpr int DPP_HALF_MIRROR = 0x141; // lane i <-> 7 - i within 8 lanes
-constexpr int DPP_ROR8 = 0x128;        // rotate a 16-lane row by 8
 
 __device__ __forceinline__ float shfl_xor(float x, int m) { return __shfl_xor(x, m); }
 
@@ -298,6 +285,13 @@ __device__ __forceinline__ void wait_memory_complete() {
   __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0), expcnt and lgkmcnt unconstrained
   __atomic_signal_fence(__ATOMIC_SEQ_CST);
 }
+// Wait until at most N of this wave's copies are in flight; until its LDS
+// reads have returned.
+template <int N>
+__device__ __forceinline__ void wait_copies() {
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+__device__ __forceinline__ void wait_lds() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
 __device__ __forceinline__ int arrive(float* ws, int grp) {
   return __hip_atomic_fetch_add(group_counter_ptr(ws, grp), 1, __ATOMIC_RELAXED,
                                 __HIP_MEMORY_SCOPE_AGENT);
@@ -941,326 +935,11 @@ __device__ __forceinline__ void decode_merge(const Args& a, const Slots sl, int 
 
 // ---------------------------------------------------------------- decode
 
-// Wave-private LDS slice: two page slots, each a K page (token rows, 16-byte
-// chunk x of row R at x ^ 8 (R & 1)) and a V^T page (64-byte dim-pair region
-// r, 16-byte slot i at (i + r / 4) & 3); then the probability buffer
-// p[head][16 keys] in bf16, the unit's block ids and (g = 8) the queries.
-// Returns the next queue ticket's pending value when asked to take one (see
-// the kernel's decode loop): the ticket is taken a few pages before the unit
-// ends, so that its round trip overlaps the unit's last pages.
-template <int G, bool APP>
-__device__ int decode_unit(const Args& a, const int32_t* it_g, char* wl, bool take_ticket) {
-  const int lane = threadIdx.x & 63;
-  const int kg = lane >> 3, c = lane & 7;
-  const record_ptr it = as_record(it_g);
-  const int s = it[DLFP_W_SEQ], kh = it[DLFP_W_KVHEAD];
-  const int kb = it[DLFP_W_KVBEGIN], ke = it[DLFP_W_KVEND];
-  const int nsplits = it[DLFP_W_NSPLITS];
-  const int tok = it[DLFP_W_QROW0];
-  const int newpos = it[DLFP_W_QPOS0];
-  const int first_blk = it[DLFP_W_PAGE0], second_blk = it[DLFP_W_PAGE1];
-  const int grp = it[DLFP_W_GROUP], wsgroup = it[DLFP_W_WSGROUP], split = it[DLFP_W_SPLIT];
-  const int32_t* bt = a.block_table + (int64_t)s * a.max_blocks;
-  uint16_t* pbuf = reinterpret_cast<uint16_t*>(wl + 2 * DEC_PAGE_SLOT);
-  int32_t* ptab = reinterpret_cast<int32_t*>(wl + 2 * DEC_PAGE_SLOT + 16 * 16 * 2);
-
-  // Page pipeline.  Pages reach the slot's LDS by direct global-to-LDS copies
-  // (no registers, no staging writes); each lane's source chunk is chosen so
-  // that the bytes land in the swizzled layout above.  Without a prefill share
-  // in the launch, page p + 2 is issued as soon as page p has been consumed,
-  // so one to two pages (8-16 KiB) per wavefront stay in flight (HBM delivers
-  // 6.0 TB/s to 8 wavefronts per CU with 8-16 KiB each in flight in a probe,
-  // 5.3 TB/s with 4 KiB).  Beside a prefill share, page p + 1 is issued when
-  // page p has landed, one page ahead: a deeper queue makes the prefill tiles
-  // wait longer for their loads (measured 3.6-5.5% longer iterations for
-  // chunks of 64-256 tokens).  A block id outside the pool is replaced by
-  // block 0 after raising the error word.
-  const bool deep = a.deep != 0;
-  const int p_begin = kb / PAGE, p_end = (ke + PAGE - 1) / PAGE;
-  const int npages = p_end - p_begin;
-  uint32_t kofs[4], vofs[4];
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const int ck = 64 * j + lane;  // LDS chunk this lane fills
-    const int R = ck >> 4, xs = ck & 15;
-    kofs[j] = R * 256 + ((xs ^ ((R & 1) << 3)) << 4);
-    const int rg = ck >> 2, si = ((ck & 3) - (rg >> 2)) & 3;
-    vofs[j] = (rg * 4 + si) * 16;
-  }
-  const uint32_t lds_wave = (uint32_t)uniform((int)lds_addr(wl));
-  auto issue_block = [&](int raw, int slot) {
-    const bool ok = (unsigned)raw < (unsigned)a.num_blocks;
-    if (!ok && lane == 0) raise_error(a.ws);
-    const int64_t base = ((int64_t)(ok ? raw : 0) * a.hkv + kh) * PAGE_ELEMS;
-    const char* ksrc = reinterpret_cast<const char*>(a.kc + base);
-    const char* vsrc = reinterpret_cast<const char*>(a.vc + base);
-    const uint32_t dst = lds_wave + uniform(slot) * DEC_PAGE_SLOT;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      lds_copy16_nt(ksrc + kofs[j], dst + j * 1024);
-      lds_copy16_nt(vsrc + vofs[j], dst + PAGE_ELEMS * 2 + j * 1024);
-    }
-  };
-  auto issue = [&](int p, int slot) { issue_block(uniform(ptab[p - p_begin]), slot); };
-  // Vector-memory operations complete in issue order, so allowing the 8
-  // copies of the next page to stay outstanding waits for this one.
-  auto wait_page = [&](bool next_in_flight) {
-    __atomic_signal_fence(__ATOMIC_SEQ_CST);
-    if (next_in_flight)
-      __builtin_amdgcn_s_waitcnt(0x0F78);  // vmcnt(8)
-    else
-      __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
-    __atomic_signal_fence(__ATOMIC_SEQ_CST);
-  };
-
-  // Prologue, one memory round trip after the work record: the first page
-  // (its block id comes with the record), the queries, the unit's block ids
-  // and (append launches) the new token's key and values all go out together,
-  // then the second page when two are kept in flight.  Queries of g <= 4 heads
-  // stay in registers (lane uses dims [8c, 8c + 8) and [64 + 8c, 64 + 8c + 8));
-  // for g = 8 they go to the wave's LDS slice (each read is an 8-address
-  // broadcast).  The append launch's unit whose keys end with the sequence's
-  // new token (position QPOS0) loads that token's key row (lanes 0-15, 16
-  // bytes each) and its values of dims 2 lane, 2 lane + 1, writes them to
-  // their slot, and puts them into the landed page in place of what the cache
-  // held there.
-  issue_block(first_blk, 0);
-  constexpr bool Q_IN_LDS = G >= 8;
-  constexpr int QR = Q_IN_LDS ? 1 : G;
-  u32x4_t qa[QR], qb[QR];
-  uint16_t* qlds =
-      reinterpret_cast<uint16_t*>(wl + 2 * DEC_PAGE_SLOT + 16 * 16 * 2 + DEC_PTAB * 4);
-  const uint16_t* qp = a.q + ((int64_t)tok * a.hq + kh * G) * D;
-  constexpr int QCH = Q_IN_LDS ? G * D / 8 / 64 : 1;  // 16-byte query chunks per lane (g = 8)
-  u32x4_t qv[QCH];
-  if constexpr (Q_IN_LDS) {
-#pragma unroll
-    for (int k = 0; k < QCH; ++k)
-      qv[k] = *reinterpret_cast<const u32x4_t*>(qp + 8 * (lane + 64 * k));
-  } else {
-#pragma unroll
-    for (int h = 0; h < G; ++h) {
-      qa[h] = *reinterpret_cast<const u32x4_t*>(qp + h * D + 8 * c);
-      qb[h] = *reinterpret_cast<const u32x4_t*>(qp + h * D + 64 + 8 * c);
-    }
-  }
-  constexpr int PTV = DEC_PTAB / 64;
-  int ptv[PTV];
-#pragma unroll
-  for (int k = 0; k < PTV; ++k) {
-    const int i = lane + 64 * k;
-    ptv[k] = i < npages ? bt[p_begin + i] : 0;
-  }
-  const bool own_new = APP && newpos < ke;
-  const int new_page = newpos / PAGE, new_off = newpos % PAGE;
-  u32x4_t kn = {0u, 0u, 0u, 0u};
-  uint32_t vn = 0u;
-  if (own_new) {
-    const int64_t src = ((int64_t)tok * a.hkv + kh) * D;
-    if (lane < 16) kn = *reinterpret_cast<const u32x4_t*>(a.k_new + src + 8 * lane);
-    vn = *reinterpret_cast<const uint32_t*>(a.v_new + src + 2 * lane);
-  }
-  if (deep && npages > 1) issue_block(second_blk, 1);
-  wait_memory_complete();  // everything above has landed
-  if constexpr (Q_IN_LDS) {
-#pragma unroll
-    for (int k = 0; k < QCH; ++k) *reinterpret_cast<u32x4_t*>(qlds + 8 * (lane + 64 * k)) = qv[k];
-  }
-#pragma unroll
-  for (int k = 0; k < PTV; ++k)
-    if (lane + 64 * k < npages) ptab[lane + 64 * k] = ptv[k];
-  wave_sync();
-  if (own_new) {
-    const int raw = ptab[new_page - p_begin];
-    if ((unsigned)raw < (unsigned)a.num_blocks) {
-      const int64_t base = ((int64_t)raw * a.hkv + kh) * PAGE_ELEMS;
-      uint16_t* kc = const_cast<uint16_t*>(a.kc);
-      uint16_t* vc = const_cast<uint16_t*>(a.vc);
-      if (lane < 16) *reinterpret_cast<u32x4_t*>(kc + base + new_off * D + 8 * lane) = kn;
-      vc[base + (2 * lane) * PAGE + vt_pos(new_off)] = (uint16_t)(vn & 0xFFFFu);
-      vc[base + (2 * lane + 1) * PAGE + vt_pos(new_off)] = (uint16_t)(vn >> 16);
-    }
-  }
-  float m[G], l[G], o0[G], o1[G];
-#pragma unroll
-  for (int h = 0; h < G; ++h) {
-    m[h] = NEG_BIG;
-    l[h] = 0.f;
-    o0[h] = 0.f;
-    o1[h] = 0.f;
-  }
-  // Queue mode: the next ticket is taken a few pages before the unit ends.
-  int ticket_v = 0;
-  const int ticket_page = max(p_begin, p_end - 4);
-
-  auto process = [&](int p, int slot) {
-    char* kl = wl + slot * DEC_PAGE_SLOT;
-    char* vl = kl + PAGE_ELEMS * 2;
-    wait_page(deep && p + 1 < p_end);
-    wave_sync();
-    if (!deep && p + 1 < p_end) issue(p + 1, slot ^ 1);  // that slot was consumed
-    if (take_ticket && p == ticket_page && lane == 0)
-      ticket_v = __hip_atomic_fetch_add(header_word(a.ws, HDR_TICKET), 1, __ATOMIC_RELAXED,
-                                        __HIP_MEMORY_SCOPE_AGENT);
-    if (p * PAGE + PAGE > ke) {
-      // Values past the unit's last key are zeroed (a probability of 0 times
-      // a NaN left in an unused slot would still be NaN).
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int ck = 64 * j + lane;
-        const int rg = ck >> 2, si = ((ck & 3) - (rg >> 2)) & 3;
-        u32x4_t* v = reinterpret_cast<u32x4_t*>(vl + ck * 16);
-        *v = mask_elems(*v, ke, [&](int e) { return p * PAGE + vt_pos(8 * (si & 1) + e); });
-      }
-    }
-    if (own_new && p == new_page) {
-      if (lane < 16)
-        *reinterpret_cast<u32x4_t*>(kl + new_off * 256 + ((lane ^ ((new_off & 1) << 3)) << 4)) = kn;
-      // region lane holds dim 2 lane in slots 0-1 and dim 2 lane + 1 in slots 2-3
-      const int sp = vt_pos(new_off), half = sp >> 3;
-      char* v0 = vl + lane * 64 + (((half + (lane >> 2)) & 3) << 4) + 2 * (sp & 7);
-      char* v1 = vl + lane * 64 + (((2 + half + (lane >> 2)) & 3) << 4) + 2 * (sp & 7);
-      *reinterpret_cast<uint16_t*>(v0) = (uint16_t)(vn & 0xFFFFu);
-      *reinterpret_cast<uint16_t*>(v1) = (uint16_t)(vn >> 16);
-    }
-    wave_sync();  // fixed-up page visible to every lane
-
-    // Keys 8 st + kg of the page (st = 0, 1): each lane holds 16 dims of both.
-    u32x4_t kv[2][2];
-#pragma unroll
-    for (int st = 0; st < 2; ++st) {
-      const int R = 8 * st + kg;
-      kv[st][0] = *reinterpret_cast<const u32x4_t*>(kl + R * 256 + ((c ^ ((R & 1) << 3)) << 4));
-      kv[st][1] =
-          *reinterpret_cast<const u32x4_t*>(kl + R * 256 + (((c + 8) ^ ((R & 1) << 3)) << 4));
-    }
-    const bool valid0 = p * PAGE + kg < ke, valid1 = p * PAGE + 8 + kg < ke;
-    // One head at a time: scores (dot products summed over the 8 lanes of a
-    // key), online-softmax update, probabilities to LDS, accumulator rescale.
-#pragma unroll
-    for (int h = 0; h < G; ++h) {
-      u32x4_t qah, qbh;
-      if constexpr (Q_IN_LDS) {
-        qah = *reinterpret_cast<const u32x4_t*>(qlds + h * D + 8 * c);
-        qbh = *reinterpret_cast<const u32x4_t*>(qlds + h * D + 64 + 8 * c);
-      } else {
-        qah = qa[h];
-        qbh = qb[h];
-      }
-      float sc[2];
-#pragma unroll
-      for (int st = 0; st < 2; ++st) {
-        float acc = 0.f;
-#pragma unroll
-        for (int w = 0; w < 4; ++w) acc = dot2(qah[w], kv[st][0][w], acc);
-#pragma unroll
-        for (int w = 0; w < 4; ++w) acc = dot2(qbh[w], kv[st][1][w], acc);
-        acc += dpp<DPP_XOR1>(acc);
-        acc += dpp<DPP_XOR2>(acc);
-        acc += dpp<DPP_HALF_MIRROR>(acc);
-        sc[st] = acc * a.scale_log2;
-      }
-      sc[0] = valid0 ? sc[0] : -__builtin_inff();
-      sc[1] = valid1 ? sc[1] : -__builtin_inff();
-      float mx = fmaxf(sc[0], sc[1]);
-      mx = fmaxf(mx, dpp<DPP_ROR8>(mx));
-      mx = max_xor16(mx);
-      mx = max_xor32(mx);
-      const float m_new = fmaxf(m[h], mx);
-      const float alpha = fexp2(m[h] - m_new);
-      m[h] = m_new;
-      const float p0 = fexp2(sc[0] - m_new), p1 = fexp2(sc[1] - m_new);
-      l[h] = l[h] * alpha + (c == 0 ? p0 + p1 : 0.f);
-      o0[h] *= alpha;
-      o1[h] *= alpha;
-      if (c == (h & 7)) {
-        pbuf[h * 16 + vt_pos(kg)] = __builtin_bit_cast(uint16_t, (__bf16)p0);
-        pbuf[h * 16 + vt_pos(8 + kg)] = __builtin_bit_cast(uint16_t, (__bf16)p1);
-      }
-      if constexpr (G >= 8) __builtin_amdgcn_sched_barrier(0);  // bound live ranges per head
-    }
-    wave_sync();  // probabilities visible to every lane
-    // O += P V: lane owns dims 2 lane and 2 lane + 1.
-    u32x4_t vr[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-      vr[i] = *reinterpret_cast<const u32x4_t*>(vl + lane * 64 + (((i + (lane >> 2)) & 3) << 4));
-#pragma unroll
-    for (int h = 0; h < G; ++h) {
-      const u32x4_t pp0 = *reinterpret_cast<const u32x4_t*>(pbuf + h * 16);
-      const u32x4_t pp1 = *reinterpret_cast<const u32x4_t*>(pbuf + h * 16 + 8);
-      float a0 = o0[h], a1 = o1[h];
-#pragma unroll
-      for (int w = 0; w < 4; ++w) {
-        a0 = dot2(pp0[w], vr[0][w], a0);
-        a1 = dot2(pp0[w], vr[2][w], a1);
-      }
-#pragma unroll
-      for (int w = 0; w < 4; ++w) {
-        a0 = dot2(pp1[w], vr[1][w], a0);
-        a1 = dot2(pp1[w], vr[3][w], a1);
-      }
-      o0[h] = a0;
-      o1[h] = a1;
-      if constexpr (G >= 8) __builtin_amdgcn_sched_barrier(0);
-    }
-    wave_sync();  // every lane done reading the slot before it is refilled
-    if (deep && p + 2 < p_end) issue(p + 2, slot);
-  };
-
-  for (int p = p_begin; p < p_end; p += 2) {
-    process(p, 0);
-    if (p + 1 < p_end) process(p + 1, 1);
-  }
-
-  // Row sums live on the c == 0 lanes; total them.
-#pragma unroll
-  for (int h = 0; h < G; ++h) {
-    float x = l[h];
-    x += dpp<DPP_ROR8>(x);
-    x = sum_xor16(x);
-    x = sum_xor32(x);
-    l[h] = __builtin_bit_cast(float, uniform(__builtin_bit_cast(int, x)));
-  }
-
-  const int64_t obase = ((int64_t)tok * a.hq + kh * G) * D + 2 * lane;
-  if (nsplits == 1) {
-#pragma unroll
-    for (int h = 0; h < G; ++h) {
-      const float inv = 1.f / l[h];
-      store2(a, obase + h * D, o0[h] * inv, o1[h] * inv);
-    }
-    return ticket_v;
-  }
-
-  // Partial: O[G][128], m[G], l[G].
-  const int slot_floats = slot_floats_for(G);
-  const Slots sl = group_slots(a.ws, wsgroup, nsplits, slot_floats);
-  const int my = split * slot_floats;
-#pragma unroll
-  for (int h = 0; h < G; ++h) {
-    pstore2(sl, my + h * D + 2 * lane, f32x2_t{o0[h], o1[h]});
-    if (lane == 0) {
-      pstore1(sl, my + G * D + h, m[h]);
-      pstore1(sl, my + G * D + G + h, l[h]);
-    }
-  }
-  wait_memory_complete();
-  int old = 0;
-  if (lane == 0) old = arrive(a.ws, grp);
-  old = __shfl(old, 0);
-  if (old != nsplits - 1) return ticket_v;
-
-  decode_merge<G>(a, sl, slot_floats, nsplits, obase, grp);
-  return ticket_v;
-}
-
-// ---------------------------------------------------------------- decode on the matrix cores
-
 typedef short s16x4_t __attribute__((ext_vector_type(4)));
 
-// Decode unit for g >= 2 query heads per KV head.  The unit's g heads are the
-// columns of 16x16 matrix products (padded to 16 with zero queries): per page,
+// Decode unit of a wavefront (launches whose decode workgroups drain a queue
+// beside prefill units).  The unit's g heads are the columns of 16x16 matrix
+// products (padded to 16 with zero queries): per page,
 // the scores are S^T = K Q^T (four v_mfma_f32_16x16x32_bf16 over the 128
 // dims) and the output advances by O^T += V^T P^T (eight
 // v_mfma_f32_16x16x16_bf16 over the page's 16 keys), so the VALU only forms
@@ -1274,15 +953,22 @@ typedef short s16x4_t __attribute__((ext_vector_type(4)));
 // permlane swaps; the reference maximum is raised lazily, as in the prefill
 // tiles.
 //
-// LDS page slots (two per wavefront, as for decode_unit): K page row R keeps
-// its 16-byte chunk x at position x ^ R; V^T row d (32 bytes) keeps its two
-// 16-byte halves swapped when bit 3 of d is set.  Either way the lanes that
-// LDS serves together read distinct banks.  The page pipeline, the prologue,
-// the queue tickets, the one-launch append and the split merge are those of
-// decode_unit.
+// Wave-private LDS slice: two page slots, each a K page (row R keeps its
+// 16-byte chunk x at position x ^ R) and a V^T page (32-byte row d keeps its
+// two halves swapped when bit 3 of d is set; either way the lanes that LDS
+// serves together read distinct banks), then the unit's block ids.  Pages
+// reach a slot by direct global-to-LDS copies (no registers, no staging
+// writes).  Asked for two pages in flight, page p + 2 is issued as soon as page
+// p has been consumed; otherwise page p + 1 when page p has landed: a deeper
+// queue makes the prefill tiles wait longer for their loads (measured 3.6-5.5%
+// longer iterations for chunks of 64-256 tokens).  A block id outside the pool
+// is replaced by block 0 after raising the error word.
+// Returns the next queue ticket's pending value when asked to take one (see
+// the kernel's decode loop): the ticket is taken a few pages before the unit
+// ends, so that its round trip overlaps the unit's last pages.
 template <int G, bool APP>
-__device__ int decode_unit_mfma(const Args& a, const int32_t* it_g, char* wl, bool take_ticket) {
-  static_assert(G >= 2 && G <= 16, "heads must fit the 16 columns");
+__device__ int decode_unit(const Args& a, const int32_t* it_g, char* wl, bool take_ticket) {
+  static_assert(G >= 1 && G <= 16, "heads must fit the 16 columns");
   const int lane = threadIdx.x & 63;
   const int col = lane & 15, gq = lane >> 4;
   const record_ptr it = as_record(it_g);
@@ -1294,7 +980,7 @@ __device__ int decode_unit_mfma(const Args& a, const int32_t* it_g, char* wl, bo
   const int first_blk = it[DLFP_W_PAGE0], second_blk = it[DLFP_W_PAGE1];
   const int grp = it[DLFP_W_GROUP], wsgroup = it[DLFP_W_WSGROUP], split = it[DLFP_W_SPLIT];
   const int32_t* bt = a.block_table + (int64_t)s * a.max_blocks;
-  int32_t* ptab = reinterpret_cast<int32_t*>(wl + 2 * DEC_PAGE_SLOT + 16 * 16 * 2);
+  int32_t* ptab = reinterpret_cast<int32_t*>(wl + 2 * DEC_PAGE_SLOT);
 
   const bool deep = a.deep != 0;
   const int p_begin = kb / PAGE, p_end = (ke + PAGE - 1) / PAGE;
@@ -1513,6 +1199,370 @@ __device__ int decode_unit_mfma(const Args& a, const int32_t* it_g, char* wl, bo
   return ticket_v;
 }
 
+// Decode unit of a whole workgroup ("wide": launches without prefill units).
+// Wavefront w takes the unit's 32-key blocks (two
+// pages) w, w + NW, ..., so all finish together and the unit's partial results
+// meet in LDS; only units of 4096 keys and more are still merged across
+// workgroups.  Against one unit per wavefront (each of the four then merged
+// through device memory, 2-5 us) decode-only launches take: 4 sequences of
+// 64-256 keys 10.2 -> 5.7 us, one of 8000 keys (g = 4) 26.0 -> 13 us, 100 of
+// 300-2400 keys 115.8 -> 93 us, 256 of 2048-16384 keys (g = 8) 1567 -> 1490 us.
+//
+// The unit's g heads are the columns of 16x16 matrix products (padded to 16
+// with zero queries).  Per block the scores are S^T = K Q^T (two independent
+// chains of four v_mfma_f32_16x16x32_bf16 over the 128 dims) and the output
+// advances by O^T += V^T P^T (eight of them over the 32 keys), half the
+// products, LDS reads and softmax steps per key of 16-key blocks.  Lane l owns
+// head column l % 16; its group q = l / 16 owns the eight keys at positions
+// 8 (q / 2) .. + 7 of page q % 2 (position p of a page holds token slot
+// vt_pos(p)).  Row r of the K operand of chain b is position
+// 8 (r / 8) + 4 b + r % 4 of page r / 4 % 2: the accumulator rows 4 q .. + 3 of
+// both chains are then exactly the group's keys, so the probabilities go from
+// the score accumulators straight into the B operand, and its V^T operand is
+// one 16-byte LDS read per 16 dims.
+//
+// Wave-private LDS slice: one key slot and one value slot of two pages each,
+// then the ids of the wavefront's pages.  A slot is refilled with the next
+// block as soon as its reads have returned, so its copies fly while the other
+// half of the step runs; four wavefronts then keep 64 KiB in flight, what a CU
+// can have outstanding (measured: a workgroup of four wavefronts alone on its
+// CU reads 67 GB/s, one of eight the same).  K row R of
+// page h keeps its 16-byte chunk x at position x ^ R ^ 8 h; V^T row d (32 bytes)
+// its two halves swapped when vt_swz(d): the lanes that LDS serves together
+// read distinct banks.
+template <int G, bool APP, int NW>
+__device__ void decode_wide(const Args& a, const int32_t* it_g, char* smem, int* flag) {
+  static_assert(G >= 1 && G <= 16 && G * 32 <= NW * 64, "heads");
+  const int tid = threadIdx.x, wave = uniform(tid >> 6), lane = tid & 63;
+  char* wl = smem + wave * WIDE_WAVE_LDS;
+  const int col = lane & 15, gq = lane >> 4;
+  const record_ptr it = as_record(it_g);
+  const int s = it[DLFP_W_SEQ], kh = it[DLFP_W_KVHEAD];
+  const int kb = it[DLFP_W_KVBEGIN], ke = it[DLFP_W_KVEND];
+  const int nsplits = it[DLFP_W_NSPLITS];
+  const int tok = it[DLFP_W_QROW0];
+  const int newpos = it[DLFP_W_QPOS0];
+  const int grp = it[DLFP_W_GROUP], wsgroup = it[DLFP_W_WSGROUP], split = it[DLFP_W_SPLIT];
+  const int32_t* bt = a.block_table + (int64_t)s * a.max_blocks;
+  int32_t* ptab = reinterpret_cast<int32_t*>(wl + 2 * WIDE_SLOT);
+
+  const int first_page = kb / PAGE;
+  const int npages = (ke + PAGE - 1) / PAGE - first_page, nblocks = (npages + 1) >> 1;
+  const int mine = nblocks > wave ? (nblocks - wave + NW - 1) / NW : 0;
+  // Page h of this wavefront's block i (the unit's last page past its end);
+  // whether the block has both pages.
+  auto page_of = [&](int i, int h) { return min(2 * (wave + NW * i) + h, npages - 1); };
+  auto has_both = [&](int i) { return 2 * (wave + NW * i) + 1 < npages; };
+
+  uint32_t kofs[2][4], vofs[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const int ck = 64 * j + lane;  // LDS chunk of a page this lane fills
+    const int R = ck >> 4, xs = ck & 15;
+    kofs[0][j] = R * 256 + ((xs ^ R) << 4);
+    kofs[1][j] = R * 256 + ((xs ^ R ^ 8) << 4);
+    const int d = ck >> 1, hs = ck & 1;
+    vofs[j] = d * 32 + ((hs ^ vt_swz(d)) << 4);
+  }
+  const uint32_t lds_wave = (uint32_t)uniform((int)lds_addr(wl));
+  // Element offset of a page (same in both caches); a block id outside the
+  // pool is replaced by block 0 after raising the error word.
+  auto page_off = [&](int raw) -> int64_t {
+    const bool ok = (unsigned)raw < (unsigned)a.num_blocks;
+    if (!ok && lane == 0) raise_error(a.ws);
+    return ((int64_t)(ok ? raw : 0) * a.hkv + kh) * PAGE_ELEMS;
+  };
+  auto copy_page = [&](const uint16_t* page, const uint32_t* off, uint32_t dst) {
+    const char* src = reinterpret_cast<const char*>(page);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) lds_copy16_nt(src + off[j], dst + j * 1024);
+  };
+  // A last block of one page leaves the other half of its slots as it is (its
+  // keys are masked, its values zeroed).
+  auto issue_k = [&](int64_t p0, int64_t p1, bool both) {
+    copy_page(a.kc + p0, kofs[0], lds_wave);
+    if (both) copy_page(a.kc + p1, kofs[1], lds_wave + WIDE_SLOT / 2);
+  };
+  auto issue_v = [&](int64_t p0, int64_t p1, bool both) {
+    copy_page(a.vc + p0, vofs, lds_wave + WIDE_SLOT);
+    if (both) copy_page(a.vc + p1, vofs, lds_wave + WIDE_SLOT + WIDE_SLOT / 2);
+  };
+  // Prologue, after the work record: wavefront 0's first block (the ids of the
+  // unit's first two pages come with the record).
+  int64_t p0 = 0, p1 = 0;
+  if (wave == 0) {
+    p0 = page_off(it[DLFP_W_PAGE0]);
+    p1 = npages > 1 ? page_off(it[DLFP_W_PAGE1]) : p0;
+    issue_k(p0, p1, npages > 1);
+    issue_v(p0, p1, npages > 1);
+  }
+  // With it go out the ids of the wavefront's pages, the queries as the B
+  // operand (lane holds dims 32 kk + 8 gq .. + 7 of its head column, zero past
+  // the g heads) and (append launches, the wavefront with the unit's last
+  // block) the new token's key row (lanes 0-15, 16 bytes each) and its values of
+  // dims 2 lane, 2 lane + 1.
+  for (int x = lane; x < 2 * mine; x += 64) ptab[x] = bt[first_page + page_of(x >> 1, x & 1)];
+  bf16x8_t qb[4];
+  {
+    const uint16_t* qp = a.q + ((int64_t)tok * a.hq + kh * G + min(col, G - 1)) * D + 8 * gq;
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) {
+      const u32x4_t v = *reinterpret_cast<const u32x4_t*>(qp + 32 * kk);
+      qb[kk] = __builtin_bit_cast(bf16x8_t, col < G ? v : u32x4_t{0u, 0u, 0u, 0u});
+    }
+  }
+  const bool own_new =
+      APP && newpos < ke && mine > 0 && wave + NW * (mine - 1) == nblocks - 1;
+  const int new_half = (newpos / PAGE - first_page) & 1, new_off = newpos % PAGE;
+  u32x4_t kn = {0u, 0u, 0u, 0u};
+  uint32_t vn = 0u;
+  if (own_new) {
+    const int64_t src = ((int64_t)tok * a.hkv + kh) * D;
+    if (lane < 16) kn = *reinterpret_cast<const u32x4_t*>(a.k_new + src + 8 * lane);
+    vn = *reinterpret_cast<const uint32_t*>(a.v_new + src + 2 * lane);
+  }
+  wait_memory_complete();
+  wave_sync();
+
+  if (wave != 0 && mine > 0) {
+    p0 = page_off(uniform(ptab[0]));
+    p1 = page_off(uniform(ptab[1]));
+    issue_k(p0, p1, has_both(0));
+    issue_v(p0, p1, has_both(0));
+  }
+  // The new token goes to its slot (and into the landed pages below).
+  if (own_new) {
+    const int raw = uniform(ptab[2 * (mine - 1) + new_half]);
+    if ((unsigned)raw < (unsigned)a.num_blocks) {
+      const int64_t base = ((int64_t)raw * a.hkv + kh) * PAGE_ELEMS;
+      uint16_t* kc = const_cast<uint16_t*>(a.kc);
+      uint16_t* vc = const_cast<uint16_t*>(a.vc);
+      if (lane < 16) *reinterpret_cast<u32x4_t*>(kc + base + new_off * D + 8 * lane) = kn;
+      vc[base + (2 * lane) * PAGE + vt_pos(new_off)] = (uint16_t)(vn & 0xFFFFu);
+      vc[base + (2 * lane + 1) * PAGE + vt_pos(new_off)] = (uint16_t)(vn >> 16);
+    }
+  }
+
+  float m_run = NEG_BIG, l_run = 0.f;
+  f32x4_t o[8];
+#pragma unroll
+  for (int mb = 0; mb < 8; ++mb) o[mb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  const float c = a.scale_log2;
+  // This lane's K operand rows: page and slot of row `col` of each chain.
+  const int kpage = (col >> 2) & 1;
+  int krow[2], kxor[2];
+#pragma unroll
+  for (int b = 0; b < 2; ++b) {
+    const int R = vt_pos(8 * (col >> 3) + 4 * b + (col & 3));
+    krow[b] = kpage * (WIDE_SLOT / 2) + R * 256;
+    kxor[b] = R ^ (kpage << 3);
+  }
+  // Accumulator row 4 gq + i of chain b is key key_of[b] + i of the block.
+  const int key_of[2] = {16 * (gq & 1) + vt_pos(8 * (gq >> 1)),
+                         16 * (gq & 1) + vt_pos(8 * (gq >> 1) + 4)};
+  // V^T operand: row col of a 16-dim block, page gq % 2, half gq / 2.
+  const int vbyte = WIDE_SLOT + (gq & 1) * (WIDE_SLOT / 2) + col * 32 +
+                    (((gq >> 1) ^ vt_swz(col)) << 4);
+
+  for (int i = 0; i < mine; ++i) {
+    const int base = kb + 2 * PAGE * (wave + NW * i);  // first key of the block
+    const bool more = i + 1 < mine, tail = base + 2 * PAGE > ke;
+    // In flight, oldest first: this block's keys, its values (eight copies
+    // each; a block of one page, only ever the last, has four).
+    if (has_both(i))
+      wait_copies<8>();
+    else
+      wait_copies<0>();
+    if (own_new && !more) {
+      if (lane < 16)
+        *reinterpret_cast<u32x4_t*>(wl + new_half * (WIDE_SLOT / 2) + new_off * 256 +
+                                    ((lane ^ new_off ^ (new_half << 3)) << 4)) = kn;
+      wave_sync();
+    }
+    f32x4_t sacc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+    {
+      bf16x8_t kf[2][4];
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk)
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+          kf[b][kk] = *reinterpret_cast<const bf16x8_t*>(wl + krow[b] +
+                                                         (((4 * kk + gq) ^ kxor[b]) << 4));
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk)
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+          sacc[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[b][kk], qb[kk], sacc[b], 0, 0, 0);
+    }
+    wait_lds();  // the key slot is free
+    const bool both = has_both(i + 1);
+    if (more) {
+      p0 = page_off(uniform(ptab[2 * i + 2]));
+      p1 = page_off(uniform(ptab[2 * i + 3]));
+      issue_k(p0, p1, both);
+    }
+    float sc[8];
+#pragma unroll
+    for (int x = 0; x < 8; ++x) sc[x] = sacc[x >> 2][x & 3];
+    if (tail) {
+#pragma unroll
+      for (int x = 0; x < 8; ++x)
+        sc[x] = base + key_of[x >> 2] + (x & 3) < ke ? sc[x] : -__builtin_inff();
+    }
+    float mx = -__builtin_inff();
+#pragma unroll
+    for (int x = 0; x < 8; ++x) mx = fmaxf(mx, sc[x]);
+    const float m_tile = max_xor32(max_xor16(mx)) * c;
+    if (__builtin_amdgcn_ballot_w64(m_tile > m_run + RESCALE_LOG2)) {
+      const float m_new = m_tile > m_run + RESCALE_LOG2 ? m_tile : m_run;
+      const float alpha = fexp2(m_run - m_new);
+      m_run = m_new;
+      l_run *= alpha;
+#pragma unroll
+      for (int mb = 0; mb < 8; ++mb) o[mb] *= alpha;
+    }
+    // P^T rounded to bf16: this lane's keys of its head column, the B operand.
+    u32x4_t pk;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      pk[w] = pack_bf16(fexp2(__builtin_fmaf(sc[2 * w], c, -m_run)),
+                        fexp2(__builtin_fmaf(sc[2 * w + 1], c, -m_run)));
+      l_run = dot2(pk[w], 0x3F803F80u, l_run);  // two bf16 1.0
+    }
+    const bf16x8_t pb = __builtin_bit_cast(bf16x8_t, pk);
+    // The values; behind them the next block's keys may be in flight.
+    if (more && both)
+      wait_copies<8>();
+    else
+      wait_copies<0>();
+    if (tail) {
+      // Values past the unit's last key are zeroed (a probability of 0 times
+      // a NaN left in an unused slot would still be NaN).
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const int ck = 64 * (j & 3) + lane, d = ck >> 1, h = (ck & 1) ^ vt_swz(d);
+        u32x4_t* v = reinterpret_cast<u32x4_t*>(wl + WIDE_SLOT + (j >> 2) * (WIDE_SLOT / 2) +
+                                                ck * 16);
+        *v = mask_elems(*v, ke,
+                        [&](int e) { return base + PAGE * (j >> 2) + vt_pos(8 * h + e); });
+      }
+      wave_sync();
+    }
+    if (own_new && !more) {
+      const int sp = vt_pos(new_off), half = sp >> 3, d0 = 2 * lane, d1 = 2 * lane + 1;
+      char* vl = wl + WIDE_SLOT + new_half * (WIDE_SLOT / 2) + 2 * (sp & 7);
+      *reinterpret_cast<uint16_t*>(vl + d0 * 32 + ((half ^ vt_swz(d0)) << 4)) =
+          (uint16_t)(vn & 0xFFFFu);
+      *reinterpret_cast<uint16_t*>(vl + d1 * 32 + ((half ^ vt_swz(d1)) << 4)) =
+          (uint16_t)(vn >> 16);
+      wave_sync();
+    }
+    // O^T += V^T P^T, eight blocks of 16 dims.
+    {
+      bf16x8_t vf[8];
+#pragma unroll
+      for (int mb = 0; mb < 8; ++mb)
+        vf[mb] = *reinterpret_cast<const bf16x8_t*>(wl + vbyte + mb * 512);
+#pragma unroll
+      for (int mb = 0; mb < 8; ++mb)
+        o[mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[mb], pb, o[mb], 0, 0, 0);
+    }
+    wait_lds();  // the value slot is free
+    if (more) issue_v(p0, p1, both);
+  }
+
+  // Each lane group holds a quarter of its head's keys.  Then the wavefronts'
+  // results are added through LDS: quad (head, 4 mb + gq) holds dims
+  // 16 mb + 4 gq .. + 3 of the head, thread (h, q4) sums quad q4 of head h.
+  const float l_tot = sum_xor32(sum_xor16(l_run));
+  wait_memory_complete();
+  __syncthreads();  // every wavefront is done with its slots
+  f32x4_t* red = reinterpret_cast<f32x4_t*>(smem);
+  float* stat = reinterpret_cast<float*>(smem + NW * G * 512);  // m[NW][G], l[NW][G]
+  auto at = [](int w, int h, int q) { return (w * G + h) * 32 + (q ^ ((h & 7) << 2)); };
+  if (col < G) {
+#pragma unroll
+    for (int mb = 0; mb < 8; ++mb) red[at(wave, col, 4 * mb + gq)] = o[mb];
+    if (gq == 0) {
+      stat[wave * G + col] = m_run;
+      stat[NW * G + wave * G + col] = l_tot;
+    }
+  }
+  __syncthreads();
+  const int h = tid >> 5, q4 = tid & 31;
+  const bool act = tid < G * 32;
+  const int64_t out_elem = ((int64_t)tok * a.hq + kh * G + h) * D + 4 * q4;
+  float M = NEG_BIG, L = 0.f;
+  f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
+  if (act) {
+#pragma unroll
+    for (int w = 0; w < NW; ++w) M = fmaxf(M, stat[w * G + h]);
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      const float e = fexp2(stat[w * G + h] - M);
+      L += e * stat[NW * G + w * G + h];
+      acc += e * red[at(w, h, q4)];
+    }
+    if (nsplits == 1) {
+      const float inv = 1.f / L;
+      store4(a, out_elem, acc[0] * inv, acc[1] * inv, acc[2] * inv, acc[3] * inv);
+    }
+  }
+  if (nsplits == 1) return;
+
+  // Partial: O[G][128], m[G], l[G]; the last arriver merges in split order.
+  const int slot_floats = slot_floats_for(G);
+  const Slots sl = group_slots(a.ws, wsgroup, nsplits, slot_floats);
+  const int my = split * slot_floats;
+  if (act) {
+    pstore4(sl, my + h * D + 4 * q4, acc);
+    if (q4 == 0) {
+      pstore1(sl, my + G * D + h, M);
+      pstore1(sl, my + G * D + G + h, L);
+    }
+  }
+  wait_memory_complete();
+  __syncthreads();  // every wave of the unit has completed its stores
+  if (tid == 0) *flag = arrive(a.ws, grp) == nsplits - 1;
+  __syncthreads();
+  if (!*flag) return;
+  if (act) {
+    // Batches of NB splits: all loads of a batch go out before any is used.
+    constexpr int NB = 16;
+    M = NEG_BIG;
+    L = 0.f;
+    acc = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    for (int j = 0; j < nsplits; j += NB) {
+      float mj[NB], lj[NB];
+      f32x4_t x[NB];
+#pragma unroll
+      for (int u = 0; u < NB; ++u) {
+        const int b = min(j + u, nsplits - 1) * slot_floats;
+        mj[u] = pload1(sl, b + G * D + h);
+        lj[u] = pload1(sl, b + G * D + G + h);
+        x[u] = pload4(sl, b + h * D + 4 * q4);
+      }
+      float mn = M;
+#pragma unroll
+      for (int u = 0; u < NB; ++u) mn = fmaxf(mn, mj[u]);  // a repeated last split changes nothing
+      const float rs = fexp2(M - mn);
+      M = mn;
+      L *= rs;
+      acc *= rs;
+#pragma unroll
+      for (int u = 0; u < NB; ++u) {
+        const float e = j + u < nsplits ? fexp2(mj[u] - mn) : 0.f;
+        L += e * lj[u];
+        acc += e * x[u];
+      }
+    }
+    const float inv = 1.f / L;
+    store4(a, out_elem, acc[0] * inv, acc[1] * inv, acc[2] * inv, acc[3] * inv);
+  }
+  if (tid == 0)
+    __hip_atomic_store(group_counter(a.ws, grp), 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // ---------------------------------------------------------------- append
 
 // Append workgroup (append launches): each wavefront writes whole append
@@ -1641,7 +1691,7 @@ __global__ __launch_bounds__(THREADS, 2) void attention_mixed_kernel(Args a) {
   if (pi >= 0) {
     const int u = xcd_remap(pi, np);
     prefill_unit<G, APP, MIXED>(a, a.work + (int64_t)u * DLFP_WORK_INTS, smem, &flag);
-  } else {
+  } else if constexpr (MIXED) {
     // Decode wavefront w of decode workgroup d starts with unit 4 d + w when
     // that is one of the first decode_static units (the workgroups resident
     // from the start); the other units form a queue that wavefronts drain one
@@ -1667,10 +1717,7 @@ __global__ __launch_bounds__(THREADS, 2) void attention_mixed_kernel(Args a) {
       // In queue mode the unit takes the next ticket itself near its end.
       const int32_t* rec = a.work + (int64_t)(a.num_prefill + t) * DLFP_WORK_INTS;
       int pending;
-      if constexpr (G >= 2)
-        pending = decode_unit_mfma<G, APP>(a, rec, wl, queue);
-      else
-        pending = decode_unit<G, APP>(a, rec, wl, queue);
+      pending = decode_unit<G, APP>(a, rec, wl, queue);
       wave_sync();
       if (!queue) break;
       t = a.decode_static + uniform(__shfl(pending, 0));
@@ -1689,6 +1736,15 @@ __global__ __launch_bounds__(THREADS, 2) void attention_mixed_kernel(Args a) {
       }
     }
   }
+}
+
+// Launches without prefill units: one wide decode unit per workgroup, longest
+// first.
+template <int G, bool APP, int NW>
+__global__ __launch_bounds__(NW * 64, 2) void decode_kernel(Args a) {
+  __shared__ __attribute__((aligned(16))) char smem[NW * WIDE_WAVE_LDS];
+  __shared__ int flag;
+  decode_wide<G, APP, NW>(a, a.work + (int64_t)blockIdx.x * DLFP_WORK_INTS, smem, &flag);
 }
 
 // Workspace of dlfp_append_attention_mixed_static: a fixed array in device
@@ -1719,17 +1775,28 @@ int compute_units() {
 
 constexpr int FUSED_APPEND_MAX_WGS = 16;
 
-template <int G, bool APP, bool MIXED>
+template <int G, bool APP>
 hipError_t launch(const Args& a, int grid, hipStream_t stream) {
-  attention_mixed_kernel<G, APP, MIXED><<<grid, THREADS, 0, stream>>>(a);
+  // Without prefill units: eight wavefronts to a unit while the units are few
+  // (a compute unit's workgroup then finishes its unit soonest: 512 units of
+  // 512-2048 keys, g = 2, 53.8 us against 58.1 with four), four, two workgroups
+  // to a compute unit, when they run in several rounds (one's prologue and sum
+  // then hide behind the other: 3656 units of the Qwen3-8B decoders 394 us
+  // against 406 with eight).
+  if (a.num_prefill == 0 && a.num_units > 4 * compute_units())
+    decode_kernel<G, APP, 4><<<a.num_units, 4 * 64, 0, stream>>>(a);
+  else if (a.num_prefill == 0)
+    decode_kernel<G, APP, 8><<<a.num_units, 8 * 64, 0, stream>>>(a);
+  else if (a.num_units > a.num_prefill)
+    attention_mixed_kernel<G, APP, true><<<grid, THREADS, 0, stream>>>(a);
+  else
+    attention_mixed_kernel<G, APP, false><<<grid, THREADS, 0, stream>>>(a);
   return hipGetLastError();
 }
 
 template <int G>
-hipError_t launch_g(const Args& a, int grid, bool app, bool mixed, hipStream_t stream) {
-  if (app)
-    return mixed ? launch<G, true, true>(a, grid, stream) : launch<G, true, false>(a, grid, stream);
-  return mixed ? launch<G, false, true>(a, grid, stream) : launch<G, false, false>(a, grid, stream);
+hipError_t launch_g(const Args& a, int grid, bool app, hipStream_t stream) {
+  return app ? launch<G, true>(a, grid, stream) : launch<G, false>(a, grid, stream);
 }
 
 // Validation, grid and launch shared by the entry points; `app` selects the
@@ -1805,14 +1872,14 @@ int launch_mixed(const dlfp_dims* dims, const dlfp_meta* meta, const int32_t* d_
     a.num_append = 0;
     a.num_waiting = 0;
   }
-  // Decode workgroups: enough to fill the resident slots of the device (two
-  // per CU), fewer when there are fewer units; they drain the decode queue.
-  // Only those that find a slot left by the append and prefill workgroups
-  // from the start (at least 64) get units by position.
+  // Decode workgroups beside prefill units: enough to fill the resident slots
+  // of the device (two per CU), fewer when there are fewer units; they drain
+  // the decode queue.  Only those that find a slot left by the append and
+  // prefill workgroups from the start (at least 64) get units by position.
   const int cus = compute_units();
   const int decode_units = meta->num_units - meta->num_prefill_units;
-  const int decode_wgs = std::min((decode_units + 3) / 4, 2 * cus);
   const int ahead = meta->num_prefill_units + a.app_wgs;
+  const int decode_wgs = std::min((decode_units + 3) / 4, 2 * cus);
   const int slots = ahead < 2 * cus ? std::max(2 * cus - ahead, 64) : 2 * cus;
   a.decode_waves = 4 * decode_wgs;
   a.decode_static = std::min(decode_units, 4 * std::min(decode_wgs, slots));
@@ -1827,14 +1894,13 @@ int launch_mixed(const dlfp_dims* dims, const dlfp_meta* meta, const int32_t* d_
     a.decode_static = std::min(decode_units, 4 * a.decode_lead);
   }
   const int grid = a.app_wgs + meta->num_prefill_units + decode_wgs;
-  const bool mixed = meta->num_prefill_units > 0 && decode_units > 0;
   (void)hipGetLastError();
   hipError_t e;
   switch (g) {
-    case 1: e = launch_g<1>(a, grid, app, mixed, stream); break;
-    case 2: e = launch_g<2>(a, grid, app, mixed, stream); break;
-    case 4: e = launch_g<4>(a, grid, app, mixed, stream); break;
-    default: e = launch_g<8>(a, grid, app, mixed, stream); break;
+    case 1: e = launch_g<1>(a, grid, app, stream); break;
+    case 2: e = launch_g<2>(a, grid, app, stream); break;
+    case 4: e = launch_g<4>(a, grid, app, stream); break;
+    default: e = launch_g<8>(a, grid, app, stream); break;
   }
   return e == hipSuccess ? DLFP_OK : DLFP_EHIP;
 }

@@ -183,6 +183,60 @@ int dlfp_build_varlen_meta(const dlfp_dims* dims, const dlfp_tuning* tuning, int
     }
     return best_sp;
   };
+  // Decode split of a launch without prefill units: one unit per workgroup of
+  // eight wavefronts, one workgroup per compute unit.  Every candidate (the
+  // longest range in k equal parts, of at least 192 keys: eight wavefronts take
+  // 256 at a time) is weighed by an estimate of the launch time in
+  // microseconds.  Up to one unit per compute unit they all stream side by
+  // side: while n units still have keys, 64 more keys of each (32 KiB) take
+  // n x 32 KiB at the device's 6.4 TB/s or 32 KiB at a compute unit's 60 GB/s,
+  // whichever is longer.  With more units the launch is bound by the bytes,
+  // plus 3 us for every round of workgroups that replaces another (its
+  // prologue and its sum over the wavefronts are not hidden).  Splitting any
+  // range costs its merge, 2.5 us.  On 48 shapes (1-256 sequences of 24-22000
+  // keys, g = 2-8) the choice is within 1.3% of the best measured split on
+  // average, and the launches take 0.79x the time of the wavefront units and
+  // splits used before (geometric mean; 8.6-10.7 -> 4.9-7 us for the smallest).
+  auto wide_split = [&]() -> int64_t {
+    const int64_t cus = std::max<int64_t>(1, resident / 8);
+    int64_t best_sp = DLFP_MAX_DECODE_UNIT_KEYS;
+    double best = std::numeric_limits<double>::infinity();
+    for (int64_t k = ceil_div(std::max<int32_t>(max_kv, 1), DLFP_MAX_DECODE_UNIT_KEYS);;
+         k += std::max<int64_t>(1, k / 4)) {
+      const int64_t sp = std::min<int64_t>(std::max<int64_t>(round_up(ceil_div(max_kv, k), 32), 192),
+                                           DLFP_MAX_DECODE_UNIT_KEYS);
+      constexpr int STEP = 64, BUCKETS = DLFP_MAX_DECODE_UNIT_KEYS / STEP;
+      int64_t units = 0, ending[BUCKETS + 1] = {0};
+      bool split = false;
+      for (int s = 0; s < num_seqs; ++s) {
+        const int32_t kl = kv_len[s], n0 = (kl + (int32_t)sp - 1) / (int32_t)sp;
+        int32_t n = n0, part = kl;
+        if (n0 > 1) {
+          part = (int32_t)round_up((kl + n0 - 1) / n0, DLFP_PAGE_SIZE);
+          n = (kl + part - 1) / part;
+          split = true;
+        }
+        units += (int64_t)n * hkv;
+        ending[(part + STEP - 1) / STEP] += (int64_t)n * hkv;
+      }
+      double e = split ? 2.5 : 0.0;
+      if (units <= cus) {
+        int64_t n = units;
+        for (int b = 1; b <= BUCKETS && n > 0; ++b) {
+          e += std::max((double)n * (STEP * 512 / 6.4e6), STEP * 512 / 60e3);
+          n -= ending[b];
+        }
+      } else {
+        e += (double)dec_keys * (512 / 6.4e6) + 3.0 * (double)units / (double)cus;
+      }
+      if (e < best) {
+        best = e;
+        best_sp = sp;
+      }
+      if (sp <= 192) break;
+    }
+    return best_sp;
+  };
   // Prefill units of the iteration for a tile size and key split.
   auto prefill_units = [&](int64_t tt, int64_t split) {
     int64_t n = 0;
@@ -303,9 +357,11 @@ int dlfp_build_varlen_meta(const dlfp_dims* dims, const dlfp_tuning* tuning, int
     // The decode share starts in the workgroup slots (two per CU, four
     // wavefronts each) that the prefill units leave, at least 64; when the
     // prefill units take them all, it runs as they retire.
-    split_d = decode_split(pre_units < resident / 4
-                               ? std::max<int64_t>(resident / 4 - pre_units, 64)
-                               : resident / 4);
+    split_d = pre_units == 0
+                  ? wide_split()
+                  : decode_split(pre_units < resident / 4
+                                     ? std::max<int64_t>(resident / 4 - pre_units, 64)
+                                     : resident / 4);
   }
 
   // Build units: prefill (KV-head-major), then decode.  Capacity: every key
@@ -405,9 +461,13 @@ int dlfp_build_varlen_meta(const dlfp_dims* dims, const dlfp_tuning* tuning, int
       emit(t.s, kh, t.t0, t.nt, t.kend, split_p, KV_GRANULE_PREFILL, DLFP_KIND_PREFILL);
   }
   const int64_t num_prefill = (int64_t)units.size();
-  // Decode units that run in a few queue rounds (more units than the wavefronts
-  // the prefill units leave, but not so many that the last round is a small
-  // part of the launch anyway) get the short tail pieces.
+  // Decode units that run in a few rounds (more units than the device takes at
+  // once, but not so many that the last round is a small part of the launch
+  // anyway) get the short tail pieces.  Beside prefill units: wavefront units,
+  // more than the wavefronts those leave.  Alone: workgroups of long units (the
+  // pieces of short ones cost more than they even out: 512 units of 512-2048
+  // keys 54 -> 67 us; 304 of 1024-4096 keys 78.8 -> 76.0 us, 1608 of the
+  // Qwen3-8B decoders 396 -> 394 us).
   bool decode_tail = false;
   if (!tn.decode_split_tokens) {
     int64_t n_dec = 0;
@@ -415,7 +475,9 @@ int dlfp_build_varlen_meta(const dlfp_dims* dims, const dlfp_tuning* tuning, int
       if (q_len[s] == 1) n_dec += hkv * ceil_div(kv_len[s], split_d);
     const int64_t slots_d = num_prefill < resident / 4
                                 ? std::max<int64_t>(resident / 4 - num_prefill, 64) : resident / 4;
-    decode_tail = n_dec > 4 * slots_d && n_dec <= 24 * slots_d;
+    const int64_t cus_d = std::max<int64_t>(1, resident / 8);
+    decode_tail = num_prefill > 0 ? n_dec > 4 * slots_d && n_dec <= 24 * slots_d
+                                  : n_dec > cus_d && n_dec <= 8 * cus_d && dec_keys >= 2048 * n_dec;
   }
   for (int s = 0; s < num_seqs; ++s) {
     if (q_len[s] != 1) continue;
@@ -535,10 +597,9 @@ int dlfp_build_varlen_meta(const dlfp_dims* dims, const dlfp_tuning* tuning, int
   else if (tn.prefill_lead_units == 0 && n_dec_units > 0 && num_prefill > cus)
     lead = cus;
   meta->prefill_lead_units = (int32_t)lead;
-  // Decode page depth: two pages in flight without a prefill share; beside
-  // one, one page (deeper decode queues delay the prefill tiles' loads; on the
-  // Qwen3-32B sweep a second page gained nothing at p_t <= 1024 and lost 3-5%
-  // at larger chunks).
+  // Decode page depth of a wavefront's unit: one page (deeper decode queues
+  // delay the prefill tiles' loads; on the Qwen3-32B sweep a second page gained
+  // nothing at p_t <= 1024 and lost 3-5% at larger chunks).
   const int depth = tn.decode_pages_in_flight ? tn.decode_pages_in_flight
                                               : (num_prefill == 0 ? 2 : 1);
   meta->decode_pages_in_flight = depth;

@@ -399,3 +399,41 @@ def test_random_mix(dev, ws, i):
     assert D.dlfp_workspace_error(ws.buf) == 0
     assert not ws.buf[:D.WORKSPACE_PARTIALS].view(torch.int32).cpu().numpy().any()
     _compare(_to64(out), seqs, f"random mix {i}")
+
+
+# Contexts around one page, one 32-key block, a block of every wavefront, an odd number
+# of pages and the longest unit.
+WIDE_CONTEXTS = [1, 15, 16, 17, 31, 32, 33, 48, 49, 64, 97, 255, 256, 257, 272, 513, 1040, 4097]
+
+
+@pytest.mark.parametrize("g,hkv,split,fused", [(1, 4, 0, True), (2, 8, 0, False), (4, 8, 48, True),
+                                               (8, 8, 0, True), (8, 1, 4096, False),
+                                               (2, 2, 16, True), (4, 2, 0, True)])
+def test_decode_only_units_of_a_workgroup(dev, ws, g, hkv, split, fused):
+    """Decode units served by a whole workgroup: every context above alone in its
+    units, cut at odd pages and automatically, new tokens in either half of a
+    block, the rest of every page NaN."""
+    shape = wl.AttnShape(g * hkv, hkv)
+    seqs = _seqs(shape, [(1, n) for n in WIDE_CONTEXTS], seed=60 + g + split)
+    it = rt.Iteration(D.make_dims(g * hkv, hkv), seqs, _pool_for(seqs), 9, dev,
+                      fill_bits=rt.BF16_NAN_BITS, tuning=D.dlfp_tuning(split, 0, 0))
+    out = torch.full((len(seqs), g * hkv, 128), float("nan"), dtype=torch.float32, device=dev)
+    it.run(ws, SCALE, out=out, fused=fused)
+    torch.cuda.synchronize()
+    assert D.dlfp_workspace_error(ws.buf) == 0
+    assert not ws.buf[:D.WORKSPACE_PARTIALS].view(torch.int32).cpu().numpy().any()
+    _compare(_to64(out), seqs, f"wide decode g={g} hkv={hkv} split={split}")
+
+
+@pytest.mark.parametrize("g", [1, 8])
+def test_decode_only_many_units(dev, ws, g):
+    """More units than four per compute unit: workgroups of four wavefronts."""
+    shape = wl.AttnShape(8 * g, 8)
+    seqs = _seqs(shape, [(1, 1 + (37 * i) % 300) for i in range(132)], seed=70 + g)
+    it = rt.Iteration(D.make_dims(8 * g, 8), seqs, _pool_for(seqs), 10, dev,
+                      fill_bits=rt.BF16_NAN_BITS)
+    assert it.batch.meta.num_units > 1024
+    out = it.run(ws, SCALE, torch.float32, fused=True)
+    torch.cuda.synchronize()
+    assert not ws.buf[:D.WORKSPACE_PARTIALS].view(torch.int32).cpu().numpy().any()
+    _compare(_to64(out), seqs, f"many wide units g={g}")
