@@ -117,18 +117,23 @@ typedef struct {
 
 /* How the attention launch splits key ranges (split-K).  Zero fields pick
  * the built-in policy.  Prefill: a launch too small to give every compute
- * unit a workgroup at 1024-key splits (decode workgroups counted) is
- * latency-bound and takes tiles of 32 rows (32 / g tokens) with the shortest
- * of 256, 512 or 1024-key splits that keeps its workgroups within two per
- * compute unit; otherwise, when the launch has a decode share, the prefill
- * takes the tallest tile of 128, 64 or 32 rows whose units, at the shortest
- * split of at least 1024 keys keeping them at most one per compute unit, come
- * within 1/16 of that count (32 rows when none does); a prefill share alone
+ * unit a workgroup at 1024-key splits is latency-bound and takes tiles of 32
+ * rows (32 / g tokens), whole or at the split of 4096, 2048, 1024, 512 or 256
+ * keys that minimises an estimate of the launch time with its workgroups
+ * within two per compute unit; otherwise, when the launch has a decode share,
+ * the prefill takes the tallest tile of 128, 64 or 32 rows whose units, at the
+ * shortest split of at least 1024 keys keeping them at most one per compute
+ * unit, come within 1/16 of that count (when a lower tile would have more
+ * units than that even unsplit, 128 rows at the shortest split giving at most
+ * one and a half per compute unit; else 32 rows); a prefill share alone
  * takes 128-row tiles and the split (a multiple of 64 keys, at least 1024)
  * that minimises an estimate of the launch time.  Without a prefill share a
  * decode unit is the work of a workgroup, and the decode split is the one in
  * equal parts (of at least 192 keys) that minimises an estimate of the launch
- * time.  Beside a prefill share a decode unit is a wavefront's, and the split
+ * time.  So it is beside a prefill share that leaves workgroup slots (two per
+ * compute unit) for all of them, when the estimate is under 0.9 of that of
+ * wavefront units; else a decode unit beside a prefill share is a wavefront's
+ * (also when split into units of up to 128 keys), and the split
  * is either sqrt(256 W / F) keys for W decode keys over the F wavefronts of the
  * workgroup slots the prefill units leave (several queue rounds), or the
  * split that fits one round and best evens the decode workgroups over the
@@ -206,7 +211,9 @@ enum {
   DLFP_W_QROW0 = 12,   /* packed row of the unit's first token in q and out:
                           cu_q[seq] + QTOK0 */
   DLFP_W_QPOS0 = 13,  /* position of the unit's first token: q_pos0[seq] + QTOK0 */
-  DLFP_W_PAGE0 = 14,  /* decode units: block id of the unit's first page (KVBEGIN / 16) */
+  DLFP_W_PAGE0 = 14,  /* decode units: block id of the unit's first page (KVBEGIN / 16);
+                         prefill units: 1 when every tile of the list has at most 32
+                         rows, else 0 */
   DLFP_W_PAGE1 = 15   /* decode units: block id of its second page, -1 if it has one page */
 };
 enum { DLFP_KIND_PREFILL = 0, DLFP_KIND_DECODE = 1, DLFP_KIND_APPEND = 2 };
@@ -286,7 +293,9 @@ int dlfp_attention_mixed(const dlfp_dims* dims, const dlfp_meta* meta, const int
  * records) are written by the first workgroups of the grid -- 8 per 64
  * records; each writes its XCD's L2 back when done -- and count themselves
  * done on a workspace word; a prefill unit waits for that count, with a bounded poll,
- * before it loads the first page holding a new token.  The wait cannot hang:
+ * before it loads the first page holding a new token.  (Units of at most 32
+ * rows, unless wavefronts' decode units run beside them, read the new tokens
+ * from k_new / v_new and neither wait nor count.)  The wait cannot hang:
  * a poll that runs out raises the workspace error word (value 2) and the
  * launch finishes with undefined output.  The last of the waiting prefill
  * units to finish zeroes the words again.  When the records would need more

@@ -4,8 +4,9 @@
 // the chunk) of Eq. 1, Sec. 2.1, served by one grid.
 //
 // Grid: the work list's prefill units first, one 256-thread workgroup each,
-// then decode units, four per workgroup (one per wavefront); a launch without
-// prefill units gives each decode unit a workgroup.
+// then decode units: four per workgroup (one per wavefront), or one when the
+// launch has no prefill units or is so small that all its workgroups are
+// resident at once.
 //
 // Prefill unit = (sequence, KV head, tile of 128 query rows, key split).
 // Rows are the tile's tokens x the g query heads sharing the KV head, so each
@@ -20,7 +21,9 @@
 // accumulator layout of S^T is already the B-operand layout of the PV
 // product, so P never leaves registers.  K/V tiles are double-buffered in LDS
 // (one barrier per tile), with XOR swizzles that keep the 16 lanes of each
-// LDS access phase on distinct banks.
+// LDS access phase on distinct banks.  Tiles of at most 32 rows, where three
+// of the four wavefronts would idle, split the keys over the wavefronts
+// instead (prefill_small).
 //
 // Decode unit = (sequence, KV head, key split).  Memory-bound: pages of K and V
 // reach LDS by fully coalesced, non-temporal 16-byte copies while earlier ones
@@ -37,7 +40,8 @@
 // launch): a decode unit takes its own new token from k_new / v_new into its
 // staged last page and stores it to its slot; leading append workgroups write
 // the prompt tokens, and prefill units wait for them before loading a page
-// that holds a new token.  Instantiated with MIXED (a launch with both
+// that holds a new token (units of at most 32 rows take the new tokens from
+// k_new / v_new and do not wait).  Instantiated with MIXED (a launch with both
 // shares), the prefill tile loop issues its QK products in the order that
 // suits a wavefront sharing its SIMD with a decode wavefront.
 #include <hip/hip_runtime.h>
@@ -78,9 +82,17 @@ constexpr int WIDE_WAVE_LDS = 2 * WIDE_SLOT + DEC_PTAB;  // a quarter of a unit'
 constexpr int LDS_BYTES = PRE_LDS > 4 * DEC_WAVE_LDS ? PRE_LDS : 4 * DEC_WAVE_LDS;
 // Two workgroups per CU (160 KiB of LDS).
 static_assert(2 * (LDS_BYTES + 16) <= 160 * 1024, "two workgroups must share a CU");
+// Small prefill units: rows, keys of a block, and per wave one slot each of a
+// block's keys and values plus the ids of its pages (two per block, every
+// fourth block of the unit).
+constexpr int SMALL_ROWS = 32, SMALL_KEYS = 32;
+constexpr int SMALL_SLOT = SMALL_KEYS * D * 2;
+constexpr int SMALL_WAVE_LDS = 2 * SMALL_SLOT + DLFP_MAX_PREFILL_UNIT_KEYS / PAGE / 4 * 4;
 constexpr float NEG_BIG = -1.0e30f;
 constexpr float LOG2E = 1.4426950408889634f;
-
+static_assert(4 * WIDE_WAVE_LDS <= LDS_BYTES, "wide decode slices must fit the shared buffer");
+static_assert(4 * SMALL_WAVE_LDS <= LDS_BYTES, "small prefill slices must fit the shared buffer");
+static_assert(4 * 1024 * 16 + 2 * 4 * 32 * 4 <= LDS_BYTES, "partial results of the four waves");
 
 struct Args {
   const int32_t* work;
@@ -102,6 +114,7 @@ struct Args {
   int32_t lead;          // prefill workgroups before the first decode workgroup
   int32_t decode_lead;   // decode workgroups before the remaining prefill ones
   int32_t deep;          // decode wavefronts keep two pages in flight
+  int32_t wide;          // a decode unit beside prefill units is the work of a workgroup
   float scale_log2;      // softmax scale * log2(e)
   // Append launches only: this iteration's keys and values [tokens][hkv][128],
   // the leading workgroups that write the append records stored after the
@@ -173,6 +186,11 @@ __device__ __forceinline__ record_ptr as_record(const int32_t* p) {
   const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
   return (record_ptr)(((uint64_t)hi << 32) | lo);
 }
+// A whole record in one scalar load.
+typedef int32_t record_t __attribute__((ext_vector_type(16), aligned(4)));
+__device__ __forceinline__ record_t load_record(const int32_t* p) {
+  return *(const __attribute__((address_space(4))) record_t*)as_record(p);
+}
 
 // Lanes of one wavefront hand data to each other through LDS.  The hardware
 // runs a wave's LDS operations in order; this keeps the compiler from moving a
@@ -193,7 +211,7 @@ __device__ __forceinline__ int* group_counter_ptr(float* ws, int grp) {
 __device__ __forceinline__ int* header_word(float* ws, int i) { return reinterpret_cast<int*>(ws) + i; }
 constexpr int HDR_TICKET = DLFP_WORKSPACE_TICKET_WORD;
 constexpr int HDR_DONE = DLFP_WORKSPACE_DONE_WORD;
-// Append launches: append wavefronts finished, waiting prefill units finished.
+// Append launches: append workgroups finished, waiting prefill units finished.
 constexpr int HDR_APPEND = DLFP_WORKSPACE_APPEND_WORD;
 constexpr int HDR_WAITED = DLFP_WORKSPACE_WAITED_WORD;
 
@@ -461,16 +479,16 @@ __device__ __forceinline__ void prefill_merge(const Args& a, const Slots sl, int
 }
 
 // MIXED: the launch also has decode units (the QK products' issue order below).
-template <int G, bool APP, bool MIXED>
-__device__ void prefill_unit(const Args& a, const int32_t* it, char* smem, int* flag) {
+template <int G, bool APP, bool MIXED, class R>
+__device__ void prefill_unit(const Args& a, const int32_t* it, const R f, char* smem, int* flag) {
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int col = lane & 31, hi = lane >> 5;
-  const int s = it[DLFP_W_SEQ], kh = it[DLFP_W_KVHEAD];
-  const int t0 = it[DLFP_W_QTOK0], nt = it[DLFP_W_QNTOK];
-  const int kb = it[DLFP_W_KVBEGIN], ke = it[DLFP_W_KVEND];
-  const int nsplits = it[DLFP_W_NSPLITS];
+  const int s = f[DLFP_W_SEQ], kh = f[DLFP_W_KVHEAD];
+  const int t0 = f[DLFP_W_QTOK0], nt = f[DLFP_W_QNTOK];
+  const int kb = f[DLFP_W_KVBEGIN], ke = f[DLFP_W_KVEND];
+  const int nsplits = f[DLFP_W_NSPLITS];
   // First packed row and first position of the sequence's new tokens.
-  const int q0 = it[DLFP_W_QROW0] - t0, pos0 = it[DLFP_W_QPOS0] - t0;
+  const int q0 = f[DLFP_W_QROW0] - t0, pos0 = f[DLFP_W_QPOS0] - t0;
   const int32_t* bt = a.block_table + (int64_t)s * a.max_blocks;
 
   const int r = wave * 32 + col;       // this lane's row within the tile
@@ -846,6 +864,332 @@ __device__ void prefill_unit(const Args& a, const int32_t* it, char* smem, int* 
     prefill_merge<G, 4>(a, sl, slot_floats, nsplits, rows, q0 + t0, kh);
   else
     prefill_merge<G, 8>(a, sl, slot_floats, nsplits, rows, q0 + t0, kh);
+  if (tid == 0)
+    __hip_atomic_store(group_counter(a.ws, grp), 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Prefill unit of at most 32 query rows: the launches too small to fill the
+// chip, which last as long as their longest unit takes from its first load to
+// its store.  One wavefront's accumulators hold all rows, so the four
+// wavefronts split the keys: wavefront w takes 32-key blocks w, w + 4, ... of
+// the unit, each through one key slot and one value slot of its own (a slot is
+// refilled as soon as its reads have returned), without a barrier until the
+// four partial results are added through LDS.  A unit then takes 6.1 us and
+// 6.4 us per 1024 keys (the 128-row code with one of its wavefronts at work:
+// 10 us and 14 us), and new tokens are read where the caller put them, which
+// takes the append and the wait for it (4.7 us) off the path.  20 new tokens
+// and one decoder, g = 2: 9.5 -> 6.0 us; 128 tokens over 1000 cached, prefill
+// alone: 18.7 -> 13.9 us; with 4 decoders over 384 cached: 17.2 -> 9.5 us.
+template <int G, bool APP>
+__device__ void prefill_small(const Args& a, record_t f, char* smem, int* flag) {
+  const int tid = threadIdx.x, wave = uniform(tid >> 6), lane = tid & 63;
+  const int col = lane & 31, hi = lane >> 5;
+  const int s = f[DLFP_W_SEQ], kh = f[DLFP_W_KVHEAD];
+  const int t0 = f[DLFP_W_QTOK0], nt = f[DLFP_W_QNTOK];
+  const int kb = f[DLFP_W_KVBEGIN], ke = f[DLFP_W_KVEND];
+  const int nsplits = f[DLFP_W_NSPLITS], grp = f[DLFP_W_GROUP];
+  const int wsgroup = f[DLFP_W_WSGROUP], split = f[DLFP_W_SPLIT];
+  const int row0 = f[DLFP_W_QROW0], first_pos = f[DLFP_W_QPOS0];
+  const int32_t* bt = a.block_table + (int64_t)s * a.max_blocks;
+
+  const int tr = col / G, hh = col % G;
+  const bool row_ok = tr < nt;
+  const int lim = row_ok ? min(first_pos + tr + 1, ke) : 0;  // keys < lim are visible
+  const int lim_min = min(first_pos + 1, ke);
+
+  const int first_page = kb / PAGE, last_page = (ke - 1) / PAGE;
+  const int blocks = (ke - kb + SMALL_KEYS - 1) / SMALL_KEYS;
+  const int mine = blocks > wave ? (blocks - wave + 3) / 4 : 0;
+  // This wavefront's page h of its block i; past the unit's last page, that page.
+  auto page_index = [&](int i, int h) { return min(2 * (wave + 4 * i) + h, last_page - first_page); };
+
+  char* wl = smem + wave * SMALL_WAVE_LDS;
+  int32_t* ptab = reinterpret_cast<int32_t*>(wl + 2 * SMALL_SLOT);
+  bf16x8_t qf[8];
+  {
+    const int64_t qrow = ((int64_t)(row0 + (row_ok ? tr : 0)) * a.hq + kh * G + hh) * D;
+#pragma unroll
+    for (int kk = 0; kk < 8; ++kk)
+      qf[kk] = *reinterpret_cast<const bf16x8_t*>(a.q + qrow + 16 * kk + 8 * hi);
+  }
+  // Block ids of this wavefront's pages, two per block.
+  for (int x = lane; x < 2 * mine; x += 64) ptab[x] = bt[first_page + page_index(x >> 1, x & 1)];
+  wait_memory_complete();
+  wave_sync();
+
+  uint32_t koff[4], voff[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int rr = 4 * i + (lane >> 4);
+    koff[i] = rr * 256 + (((lane & 15) ^ rr) << 4);
+    const int d = 32 * i + (lane >> 1);
+    voff[i] = d * 32 + (((lane & 1) ^ vt_swz(d)) << 4);
+  }
+  const uint32_t lds_wave = (uint32_t)uniform((int)lds_addr(wl));
+  // Element offset of a page (same in both caches).
+  auto page_off = [&](int raw) -> int64_t {
+    const bool ok = (unsigned)raw < (unsigned)a.num_blocks;
+    if (!ok && lane == 0) raise_error(a.ws);
+    return ((int64_t)(ok ? raw : 0) * a.hkv + kh) * PAGE_ELEMS;
+  };
+  auto issue = [&](const uint16_t* cache, const uint32_t* off, int64_t p0, int64_t p1, uint32_t dst) {
+    const char* s0 = reinterpret_cast<const char*>(cache + p0);
+    const char* s1 = reinterpret_cast<const char*>(cache + p1);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) lds_copy16(s0 + off[i], dst + i * 1024);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) lds_copy16(s1 + off[i], dst + (4 + i) * 1024);
+  };
+
+  // Blocks that hold new tokens are "fresh" and come first, then the old ones
+  // (the same order whether the tokens are in the cache or not).  In an append
+  // launch every unit is small and takes new tokens from k_new and v_new, so
+  // none waits for the append records.
+  const int pos0 = first_pos - t0;
+  const bool direct = APP && a.app_wgs > 0;
+  const int fresh_block = max(0, (pos0 - kb) / SMALL_KEYS);  // the block holding position pos0
+  const int old = min(mine, fresh_block > wave ? (fresh_block - wave + 3) / 4 : 0);
+  auto first_key = [&](int i) { return kb + (wave + 4 * i) * SMALL_KEYS; };
+  // Block of step j of the loop over cached blocks.
+  const int steps = direct ? old : mine;
+  auto block_of = [&](int j) { return direct ? j : j + old < mine ? j + old : j + old - mine; };
+  const int kbase = col * 256 + ((hi ^ (col & 15)) << 4);
+  const int vbase = SMALL_SLOT + col * 32 + ((hi ^ vt_swz(col)) << 4);
+  const float c = a.scale_log2;
+  float m_run = NEG_BIG, l_run = 0.f;
+  f32x16_t o[4];
+#pragma unroll
+  for (int mb = 0; mb < 4; ++mb) o[mb] = f32x16_t{};
+
+  // Scores of a block's keys into probabilities, then O^T += V^T P^T over the
+  // value slot.
+  bf16x8_t pf[2];
+  auto softmax = [&](f32x16_t sacc, int k0) {
+    if (k0 + SMALL_KEYS > lim_min) {
+#pragma unroll
+      for (int rr = 0; rr < 16; ++rr)
+        sacc[rr] = k0 + 8 * (rr >> 2) + 4 * hi + (rr & 3) < lim ? sacc[rr] : -__builtin_inff();
+    }
+    float mx = -__builtin_inff();
+#pragma unroll
+    for (int rr = 0; rr < 16; ++rr) mx = fmaxf(mx, sacc[rr]);
+    const float m_tile = max_xor32(mx) * c;
+    if (__builtin_amdgcn_ballot_w64(m_tile > m_run + RESCALE_LOG2)) {
+      const float m_new = m_tile > m_run + RESCALE_LOG2 ? m_tile : m_run;
+      const float alpha = fexp2(m_run - m_new);
+      m_run = m_new;
+      l_run *= alpha;
+#pragma unroll
+      for (int mb = 0; mb < 4; ++mb) o[mb] *= alpha;
+    }
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk) {
+      u32x4_t pk;
+#pragma unroll
+      for (int w = 0; w < 4; ++w) {
+        const float p0 = fexp2(__builtin_fmaf(sacc[8 * kk + 2 * w], c, -m_run));
+        const float p1 = fexp2(__builtin_fmaf(sacc[8 * kk + 2 * w + 1], c, -m_run));
+        pk[w] = pack_bf16(p0, p1);
+        l_run = dot2(pk[w], 0x3F803F80u, l_run);  // two bf16 1.0
+      }
+      pf[kk] = __builtin_bit_cast(bf16x8_t, pk);
+    }
+  };
+  auto pv = [&]() {
+    bf16x8_t vf[8];
+#pragma unroll
+    for (int x = 0; x < 8; ++x)
+      vf[x] = *reinterpret_cast<const bf16x8_t*>(wl + vbase + (x >> 2) * (PAGE * 256) +
+                                                 (x & 3) * 1024);
+#pragma unroll
+    for (int x = 0; x < 8; ++x)
+      o[x & 3] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[x], pf[x >> 2], o[x & 3], 0, 0, 0);
+    wait_lds();  // the value slot is free
+  };
+
+  int64_t p0 = 0, p1 = 0;  // page offsets of the block going out
+  if (steps > 0) {
+    const int i = block_of(0);
+    p0 = page_off(uniform(ptab[2 * i]));
+    p1 = page_off(uniform(ptab[2 * i + 1]));
+    issue(a.kc, koff, p0, p1, lds_wave);
+  }
+  // Fresh blocks first, while the first old one's keys are in flight: the key
+  // operand straight from its rows (of the cache or, from position pos0 on, of
+  // k_new; keys past the unit's last re-read that one and are masked), the
+  // values of dims 2 lane and 2 lane + 1 gathered from v_new (or from their
+  // page) and packed into the value slot.
+  for (int i = direct ? old : mine; i < mine; ++i) {
+    const int k0 = first_key(i);
+    const int64_t f0 = page_off(uniform(ptab[2 * i])), f1 = page_off(uniform(ptab[2 * i + 1]));
+    // Row of the sequence's first new token in k_new and v_new, this KV head.
+    const int64_t new0 = ((int64_t)(row0 - t0) * a.hkv + kh) * D, stride = (int64_t)a.hkv * D;
+    const int key = min(k0 + col, ke - 1);
+    const uint16_t* krow = key < pos0 ? a.kc + (col < PAGE ? f0 : f1) + (col % PAGE) * D
+                                      : a.k_new + new0 + (key - pos0) * stride;
+    bf16x8_t kf[8];
+#pragma unroll
+    for (int kk = 0; kk < 8; ++kk)
+      kf[kk] = *reinterpret_cast<const bf16x8_t*>(krow + 16 * kk + 8 * hi);
+    uint32_t x[2][PAGE];
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int t = 0; t < PAGE; ++t)
+        x[h][t] = *reinterpret_cast<const uint32_t*>(
+            a.v_new + new0 + (min(max(k0 + PAGE * h + t, pos0), ke - 1) - pos0) * stride + 2 * lane);
+    f32x16_t sacc = f32x16_t{};
+#pragma unroll
+    for (int kk = 0; kk < 8; ++kk)
+      sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[kk], qf[kk], sacc, 0, 0, 0);
+    softmax(sacc, k0);
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int key0 = k0 + PAGE * h;
+      if (key0 < pos0) {  // the page's first tokens are old ones
+        const u32x4_t* row =
+            reinterpret_cast<const u32x4_t*>(a.vc + (h ? f1 : f0) + (2 * lane) * PAGE);
+        const u32x4_t w0[2] = {row[0], row[1]}, w1[2] = {row[2], row[3]};
+#pragma unroll
+        for (int t = 0; t < PAGE; ++t) {
+          const int sp = vt_pos(t);
+          const uint32_t lo = w0[sp >> 3][(sp & 7) >> 1], up = w1[sp >> 3][(sp & 7) >> 1];
+          const uint32_t was =
+              (sp & 1) ? (lo >> 16) | (up & 0xFFFF0000u) : (lo & 0xFFFFu) | (up << 16);
+          x[h][t] = key0 + t < pos0 ? was : x[h][t];
+        }
+      }
+      char* vl = wl + SMALL_SLOT + h * (PAGE * 256);
+#pragma unroll
+      for (int half = 0; half < 2; ++half) {
+        u32x4_t d0, d1;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+          const int ta = vt_pos(8 * half + 2 * w), tb = vt_pos(8 * half + 2 * w + 1);
+          const uint32_t xa = key0 + ta < ke ? x[h][ta] : 0u, xb = key0 + tb < ke ? x[h][tb] : 0u;
+          d0[w] = (xa & 0xFFFFu) | (xb << 16);
+          d1[w] = (xa >> 16) | (xb & 0xFFFF0000u);
+        }
+        const int d = 2 * lane;
+        *reinterpret_cast<u32x4_t*>(vl + d * 32 + ((half ^ vt_swz(d)) << 4)) = d0;
+        *reinterpret_cast<u32x4_t*>(vl + (d + 1) * 32 + ((half ^ vt_swz(d + 1)) << 4)) = d1;
+      }
+    }
+    wave_sync();
+    pv();
+  }
+
+  if (steps > 0) issue(a.vc, voff, p0, p1, lds_wave + SMALL_SLOT);
+  for (int j = 0; j < steps; ++j) {
+    const int k0 = first_key(block_of(j));
+    const bool more = j + 1 < steps;
+    wait_copies<8>();  // in flight, oldest first: this block's keys, its values
+    f32x16_t sacc = f32x16_t{};
+    {
+      bf16x8_t kf[8];
+#pragma unroll
+      for (int kk = 0; kk < 8; ++kk)
+        kf[kk] = *reinterpret_cast<const bf16x8_t*>(wl + (kbase ^ (kk << 5)));
+#pragma unroll
+      for (int kk = 0; kk < 8; ++kk)
+        sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[kk], qf[kk], sacc, 0, 0, 0);
+    }
+    wait_lds();  // the key slot is free
+    if (more) {
+      const int i = block_of(j + 1);
+      p0 = page_off(uniform(ptab[2 * i]));
+      p1 = page_off(uniform(ptab[2 * i + 1]));
+      issue(a.kc, koff, p0, p1, lds_wave);
+    }
+    softmax(sacc, k0);
+    if (more)
+      wait_copies<8>();  // the values; behind them the next block's keys
+    else
+      wait_copies<0>();
+    if (k0 + SMALL_KEYS > ke) {
+      // Values past the unit's last key are zeroed (a probability of 0 times a
+      // NaN left in an unused slot would still be NaN).
+#pragma unroll
+      for (int x = 0; x < 8; ++x) {
+        const int pg = x >> 2, d = 2 * lane + ((x >> 1) & 1), h = x & 1;
+        char* p = wl + SMALL_SLOT + pg * (PAGE * 256) + d * 32 + (h << 4);
+        const int half = h ^ vt_swz(d), key0 = k0 + pg * PAGE;
+        *reinterpret_cast<u32x4_t*>(p) =
+            mask_elems(*reinterpret_cast<const u32x4_t*>(p), ke,
+                       [&](int e) { return key0 + vt_pos(8 * half + e); });
+      }
+      wave_sync();
+    }
+    pv();
+    if (more) issue(a.vc, voff, p0, p1, lds_wave + SMALL_SLOT);
+  }
+
+  // Add the four wavefronts' results through LDS.  Piece (c, hi) of a row holds
+  // dims 32 (c / 4) + 8 (c % 4) + 4 hi .. + 3; thread (row, sub) of the sum takes
+  // chunks 2 sub and 2 sub + 1, 16 consecutive dims; the row is XORed with the
+  // chunk so that both sides spread over the banks.
+  l_run = sum_xor32(l_run);
+  __syncthreads();  // every wavefront is done with its slots
+  f32x4_t* red = reinterpret_cast<f32x4_t*>(smem);
+  float* stat = reinterpret_cast<float*>(smem + 4 * 1024 * 16);  // m[4][32], l[4][32]
+  auto at = [](int w, int ch, int h, int row) {
+    return w * 1024 + ch * 64 + h * 32 + (row ^ (((ch >> 1) & 7) << 1));
+  };
+#pragma unroll
+  for (int mb = 0; mb < 4; ++mb)
+#pragma unroll
+    for (int g4 = 0; g4 < 4; ++g4)
+      red[at(wave, 4 * mb + g4, hi, col)] = f32x4_t{o[mb][4 * g4], o[mb][4 * g4 + 1],
+                                                   o[mb][4 * g4 + 2], o[mb][4 * g4 + 3]};
+  if (hi == 0) {
+    stat[wave * 32 + col] = m_run;
+    stat[128 + wave * 32 + col] = l_run;
+  }
+  __syncthreads();
+  const int row = tid >> 3, sub = tid & 7, rows = nt * G;
+  float M = NEG_BIG, L = 0.f, wgt[4];
+#pragma unroll
+  for (int w = 0; w < 4; ++w) M = fmaxf(M, stat[w * 32 + row]);
+#pragma unroll
+  for (int w = 0; w < 4; ++w) {
+    wgt[w] = fexp2(stat[w * 32 + row] - M);
+    L += wgt[w] * stat[128 + w * 32 + row];
+  }
+  f32x4_t acc[4];  // pieces (2 sub, 0), (2 sub, 1), (2 sub + 1, 0), (2 sub + 1, 1)
+#pragma unroll
+  for (int x = 0; x < 4; ++x) {
+    acc[x] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int w = 0; w < 4; ++w) acc[x] += wgt[w] * red[at(w, 2 * sub + (x >> 1), x & 1, row)];
+  }
+  if (nsplits == 1) {
+    if (row < rows) {
+      const float inv = 1.f / L;
+      const int64_t orow = ((int64_t)(row0 + row / G) * a.hq + kh * G + row % G) * D + 16 * sub;
+#pragma unroll
+      for (int x = 0; x < 4; ++x)
+        store4(a, orow + 4 * x, acc[x][0] * inv, acc[x][1] * inv, acc[x][2] * inv, acc[x][3] * inv);
+    }
+    return;
+  }
+  const int slot_floats = slot_floats_for(rows);
+  const Slots sl = group_slots(a.ws, wsgroup, nsplits, slot_floats);
+  const int my = split * slot_floats;
+  if (row < rows) {
+#pragma unroll
+    for (int x = 0; x < 4; ++x)
+      pstore4(sl, my + ((2 * sub + (x >> 1)) * rows + row) * 8 + 4 * (x & 1), acc[x]);
+    if (sub == 0) {
+      pstore1(sl, my + rows * D + row, M);
+      pstore1(sl, my + rows * D + rows + row, L);
+    }
+  }
+  wait_memory_complete();
+  __syncthreads();  // every wave of the unit has completed its stores
+  if (tid == 0) *flag = arrive(a.ws, grp) == nsplits - 1;
+  __syncthreads();
+  if (!*flag) return;
+  prefill_merge<G, 8>(a, sl, slot_floats, nsplits, rows, row0, kh);
   if (tid == 0)
     __hip_atomic_store(group_counter(a.ws, grp), 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
@@ -1580,6 +1924,7 @@ __device__ void decode_wide(const Args& a, const int32_t* it_g, char* smem, int*
 // records, the workgroup then writes its L2 back (an agent-scope release) and
 // counts itself done.
 
+template <bool DIRECT>
 __device__ void append_records(const Args& a) {
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   uint16_t* kc = const_cast<uint16_t*>(a.kc);
@@ -1643,7 +1988,7 @@ __device__ void append_records(const Args& a) {
         }
     }
   }
-  if (a.num_waiting > 0) {
+  if (a.num_waiting > 0 && !(DIRECT && a.work[DLFP_W_PAGE0])) {
     wait_memory_complete();  // this wavefront's stores have reached the L2
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -1656,11 +2001,57 @@ __device__ void append_records(const Args& a) {
 
 // The append records alone, as a launch of their own (one record per
 // wavefront) ahead of the attention launch.
-__global__ __launch_bounds__(THREADS) void append_records_kernel(Args a) { append_records(a); }
+__global__ __launch_bounds__(THREADS) void append_records_kernel(Args a) {
+  append_records<false>(a);
+}
 
 // ---------------------------------------------------------------- kernel
 
-template <int G, bool APP, bool MIXED>
+// Grid: `lead` prefill workgroups, `decode_lead` decode workgroups, the other
+// prefill workgroups, the other decode workgroups.  The prefill unit of
+// workgroup b (after the append workgroups), or -1 - d for decode workgroup d.
+// The i-th prefill workgroup takes unit xcd_remap(i): decode_lead is a multiple
+// of 8, so it runs on XCD i % 8 either way.
+__device__ __forceinline__ int prefill_of(const Args& a, int b) {
+  const int np = a.num_prefill, L = a.lead, DL = a.decode_lead;
+  if (b < L) return xcd_remap(b, np);
+  if (b < L + DL) return L - 1 - b;
+  if (b < np + DL) return xcd_remap(b - DL, np);
+  return np - 1 - b;
+}
+
+// Prefill units, and decode units of a workgroup each (DECODE).  Units of few
+// rows (the records say so, for all units or none) take the code made for
+// them; a record comes in whole, so the choice costs no round trip.
+template <int G, bool APP, bool DECODE>
+__global__ __launch_bounds__(THREADS, 2) void attention_wide_kernel(Args a) {
+  __shared__ __attribute__((aligned(16))) char smem[LDS_BYTES];
+  __shared__ int flag;
+  int b = blockIdx.x;
+  if constexpr (APP) {
+    if (b < a.app_wgs) {
+      append_records<true>(a);
+      return;
+    }
+    b -= a.app_wgs;
+  }
+  const int u = prefill_of(a, b);
+  if (u >= 0) {
+    const int32_t* rec = a.work + (int64_t)u * DLFP_WORK_INTS;
+    const record_t f = load_record(rec);
+    if (f[DLFP_W_PAGE0])
+      prefill_small<G, APP>(a, f, smem, &flag);
+    else
+      prefill_unit<G, APP, DECODE>(a, rec, f, smem, &flag);
+  } else if constexpr (DECODE) {
+    decode_wide<G, APP, 4>(a, a.work + (int64_t)(a.num_prefill - 1 - u) * DLFP_WORK_INTS, smem,
+                           &flag);
+  }
+}
+
+// Prefill units of any height beside wavefronts that drain a queue of decode
+// units.
+template <int G, bool APP>
 __global__ __launch_bounds__(THREADS, 2) void attention_mixed_kernel(Args a) {
   __shared__ __attribute__((aligned(16))) char smem[LDS_BYTES];
   __shared__ int flag;
@@ -1669,7 +2060,7 @@ __global__ __launch_bounds__(THREADS, 2) void attention_mixed_kernel(Args a) {
     // Append workgroups first (a multiple of 8, so the XCD of every later
     // workgroup is unchanged by the offset).
     if (b < a.app_wgs) {
-      append_records(a);
+      append_records<false>(a);
       return;
     }
     b -= a.app_wgs;
@@ -1690,8 +2081,9 @@ __global__ __launch_bounds__(THREADS, 2) void attention_mixed_kernel(Args a) {
     d = b - np;
   if (pi >= 0) {
     const int u = xcd_remap(pi, np);
-    prefill_unit<G, APP, MIXED>(a, a.work + (int64_t)u * DLFP_WORK_INTS, smem, &flag);
-  } else if constexpr (MIXED) {
+    const int32_t* rec = a.work + (int64_t)u * DLFP_WORK_INTS;
+    prefill_unit<G, APP, true>(a, rec, rec, smem, &flag);
+  } else {
     // Decode wavefront w of decode workgroup d starts with unit 4 d + w when
     // that is one of the first decode_static units (the workgroups resident
     // from the start); the other units form a queue that wavefronts drain one
@@ -1787,10 +2179,12 @@ hipError_t launch(const Args& a, int grid, hipStream_t stream) {
     decode_kernel<G, APP, 4><<<a.num_units, 4 * 64, 0, stream>>>(a);
   else if (a.num_prefill == 0)
     decode_kernel<G, APP, 8><<<a.num_units, 8 * 64, 0, stream>>>(a);
-  else if (a.num_units > a.num_prefill)
-    attention_mixed_kernel<G, APP, true><<<grid, THREADS, 0, stream>>>(a);
+  else if (a.num_units == a.num_prefill)
+    attention_wide_kernel<G, APP, false><<<grid, THREADS, 0, stream>>>(a);
+  else if (a.wide)
+    attention_wide_kernel<G, APP, true><<<grid, THREADS, 0, stream>>>(a);
   else
-    attention_mixed_kernel<G, APP, false><<<grid, THREADS, 0, stream>>>(a);
+    attention_mixed_kernel<G, APP><<<grid, THREADS, 0, stream>>>(a);
   return hipGetLastError();
 }
 
@@ -1872,14 +2266,24 @@ int launch_mixed(const dlfp_dims* dims, const dlfp_meta* meta, const int32_t* d_
     a.num_append = 0;
     a.num_waiting = 0;
   }
-  // Decode workgroups beside prefill units: enough to fill the resident slots
-  // of the device (two per CU), fewer when there are fewer units; they drain
-  // the decode queue.  Only those that find a slot left by the append and
-  // prefill workgroups from the start (at least 64) get units by position.
+  // Decode units beside prefill units.  When all workgroups fit the resident
+  // slots of the device (two per CU) even with a workgroup to each unit, each
+  // gets one: the launch is short and its end, where a wavefront's unit streams
+  // alone at a quarter of what the compute unit could take, is most of it
+  // (g = 8, 6 decoders of 250-2000 keys beside 47 new tokens: 18.9 -> 11.8 us;
+  // g = 4, 10 of 442-3536 beside 2: 21.7 -> 17.8 us).  Not for units of up to
+  // 128 keys, one step of a workgroup, which the built-in split makes where the
+  // prefill share sets the launch time (11 decoders of 38-304 keys beside 796
+  // tokens over 858, g = 2: 34.8 us, a workgroup each 35.3 us).  Otherwise
+  // enough workgroups to fill the slots, fewer when there are fewer units;
+  // they drain the decode queue.  Only those that find a slot left by the
+  // append and prefill workgroups from the start (at least 64) get units by
+  // position.
   const int cus = compute_units();
   const int decode_units = meta->num_units - meta->num_prefill_units;
   const int ahead = meta->num_prefill_units + a.app_wgs;
-  const int decode_wgs = std::min((decode_units + 3) / 4, 2 * cus);
+  a.wide = ahead + decode_units <= 2 * cus && meta->decode_split_tokens > 128;
+  const int decode_wgs = a.wide ? decode_units : std::min((decode_units + 3) / 4, 2 * cus);
   const int slots = ahead < 2 * cus ? std::max(2 * cus - ahead, 64) : 2 * cus;
   a.decode_waves = 4 * decode_wgs;
   a.decode_static = std::min(decode_units, 4 * std::min(decode_wgs, slots));

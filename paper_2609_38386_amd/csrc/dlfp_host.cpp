@@ -197,7 +197,11 @@ int dlfp_build_varlen_meta(const dlfp_dims* dims, const dlfp_tuning* tuning, int
   // keys, g = 2-8) the choice is within 1.3% of the best measured split on
   // average, and the launches take 0.79x the time of the wavefront units and
   // splits used before (geometric mean; 8.6-10.7 -> 4.9-7 us for the smallest).
-  auto wide_split = [&]() -> int64_t {
+  // Beside `ahead` prefill and append workgroups (0: alone) the units have to
+  // fit into the slots those leave, two workgroups per compute unit, and past
+  // one unit per compute unit half of the longest unit runs alone at the end.
+  // Returns the split and the estimate (infinite: no split fits).
+  auto wide_split = [&](int64_t ahead, double* est) -> int64_t {
     const int64_t cus = std::max<int64_t>(1, resident / 8);
     int64_t best_sp = DLFP_MAX_DECODE_UNIT_KEYS;
     double best = std::numeric_limits<double>::infinity();
@@ -207,6 +211,7 @@ int dlfp_build_varlen_meta(const dlfp_dims* dims, const dlfp_tuning* tuning, int
                                            DLFP_MAX_DECODE_UNIT_KEYS);
       constexpr int STEP = 64, BUCKETS = DLFP_MAX_DECODE_UNIT_KEYS / STEP;
       int64_t units = 0, ending[BUCKETS + 1] = {0};
+      int32_t longest = 0;
       bool split = false;
       for (int s = 0; s < num_seqs; ++s) {
         const int32_t kl = kv_len[s], n0 = (kl + (int32_t)sp - 1) / (int32_t)sp;
@@ -217,8 +222,10 @@ int dlfp_build_varlen_meta(const dlfp_dims* dims, const dlfp_tuning* tuning, int
           split = true;
         }
         units += (int64_t)n * hkv;
+        longest = std::max(longest, part);
         ending[(part + STEP - 1) / STEP] += (int64_t)n * hkv;
       }
+      if (ahead > 0 && units > 2 * cus - ahead) break;  // a shorter split has more
       double e = split ? 2.5 : 0.0;
       if (units <= cus) {
         int64_t n = units;
@@ -226,6 +233,8 @@ int dlfp_build_varlen_meta(const dlfp_dims* dims, const dlfp_tuning* tuning, int
           e += std::max((double)n * (STEP * 512 / 6.4e6), STEP * 512 / 60e3);
           n -= ending[b];
         }
+      } else if (ahead > 0) {
+        e += (double)dec_keys * (512 / 6.4e6) + 0.5 * longest * (512 / 60e3);
       } else {
         e += (double)dec_keys * (512 / 6.4e6) + 3.0 * (double)units / (double)cus;
       }
@@ -235,6 +244,7 @@ int dlfp_build_varlen_meta(const dlfp_dims* dims, const dlfp_tuning* tuning, int
       }
       if (sp <= 192) break;
     }
+    *est = best;
     return best_sp;
   };
   // Prefill units of the iteration for a tile size and key split.
@@ -256,13 +266,7 @@ int dlfp_build_varlen_meta(const dlfp_dims* dims, const dlfp_tuning* tuning, int
   // that leaves some tiles whole and cuts others in two makes the launch as
   // long as the whole ones.  (Fitted to Qwen3-0.6B/8B/32B last chunks, where
   // it picks the measured best: 0.6B 2048 tokens 143 against 175 us before,
-  // 1024 tokens 83 against 102 us.)  A launch too small to give every CU a
-  // workgroup at 1024-key splits (decode units counted four to a workgroup, at
-  // the split they would take without prefill) is bound by the latency of its
-  // longest unit and of the merge of its splits: its prefill takes tiles of
-  // 32 rows (a merge then moves a quarter of the bytes) and the shortest split
-  // of 256, 512 or 1024 keys that keeps all workgroups within the two a CU
-  // holds.
+  // 1024 tokens 83 against 102 us.)
   int64_t split_p = tn.prefill_split_tokens;
   int64_t dec_wgs0 = 0;
   {
@@ -271,14 +275,74 @@ int dlfp_build_varlen_meta(const dlfp_dims* dims, const dlfp_tuning* tuning, int
       if (q_len[s] == 1) dec_wgs0 += hkv * ceil_div(kv_len[s], sd0);
     dec_wgs0 = ceil_div(dec_wgs0, 4);
   }
-  if (!split_p && !tn.prefill_tile_tokens && pre_keys > 0 &&
-      prefill_units(tile_tokens, 1024) + dec_wgs0 < resident / 8) {
+  // Append workgroups of a one-launch iteration (none when the records take a
+  // launch of their own), and the time of the decode share as wavefront units,
+  // in microseconds: its bytes, and the queue's start, last units and merges.
+  int64_t app_wgs = 0;
+  for (int s = 0; s < num_seqs; ++s)
+    if (q_len[s] != 1) app_wgs += hkv * (q_len[s] / DLFP_PAGE_SIZE + 2);
+  app_wgs = ceil_div(app_wgs, 64) * 8;
+  if (app_wgs > 16) app_wgs = 0;
+  const double wave_est = dec_keys > 0 ? (double)dec_keys * (512 / 6.4e6) + 8.0 : 0.0;
+  // Time of the prefill share in microseconds: a fixed part, the merge of its
+  // splits, and its longest unit, with the compute units' workgroups (`others`
+  // of other shares) side by side; for the code of at most 32 rows or the other.
+  auto prefill_est = [&](int64_t tt, int64_t sp, bool few_rows, int64_t others, int64_t* units) {
+    int64_t n = 0, longest = 0, parts = 1;
+    for (int s = 0; s < num_seqs; ++s) {
+      if (q_len[s] == 1) continue;
+      const int64_t pos0 = kv_len[s] - q_len[s];
+      for (int64_t t0 = 0; t0 < q_len[s]; t0 += tt) {
+        const int64_t kend = pos0 + t0 + std::min<int64_t>(tt, q_len[s] - t0);
+        const int64_t part = round_up(ceil_div(kend, ceil_div(kend, sp)), KV_GRANULE_PREFILL);
+        n += hkv * ceil_div(kend, part);
+        longest = std::max(longest, std::min(part, kend));
+        parts = std::max(parts, ceil_div(kend, part));
+      }
+    }
+    *units = n;
+    const double crowd = std::max(1.0, (double)(n + others) / (double)std::max<int64_t>(1, resident / 8));
+    return (few_rows ? 6.1 : 10.0) + (parts > 1 ? 2.4 + 0.2 * (double)parts : 0.0) +
+           (few_rows ? 0.0064 : 0.0155) * (double)longest * std::min(crowd, 2.0);
+  };
+  // A launch too small to give every CU a workgroup at 1024-key splits is bound
+  // by the latency of its longest unit and of the merge of its splits: its
+  // prefill takes tiles of 32 rows (which have code of their own, and whose
+  // merge moves a quarter of the bytes), whole or at the split that these
+  // estimates favour, all workgroups within the two a CU holds.  The decode
+  // share counts as small when its wavefront units, four to a workgroup at the
+  // split they would take without prefill, leave that room too, or when units
+  // of a workgroup fit beside the tiles and are much faster.  (Shapes of 1-160
+  // decoders of 16-30000 keys and 2-3000 new tokens over up to 12000, g = 1-8:
+  // 0.82x the launch time of the policy and code before, geometric mean of 120,
+  // none slower by more than 1.5%; prefill alone 0.75x over 36.)
+  if (!split_p && !tn.prefill_tile_tokens && pre_keys > 0) {
+    const int64_t cus = resident / 8, slots = resident / 4;
     const int small = std::max(1, 32 / g);
-    for (int64_t sp : {256, 512, 1024}) {
-      if (prefill_units(small, sp) + dec_wgs0 <= resident / 4) {
-        tile_tokens = small;
-        split_p = sp;
-        break;
+    const int64_t tall_units = prefill_units(tile_tokens, 1024);
+    const bool wave_fits = tall_units + dec_wgs0 < cus;
+    const int64_t dec_wgs = wave_fits ? dec_wgs0 : 0;
+    if (tall_units < cus && prefill_units(small, 1024) + dec_wgs <= slots) {
+      double best = std::numeric_limits<double>::infinity();
+      for (int64_t sp : {DLFP_MAX_PREFILL_UNIT_KEYS, 4096, 2048, 1024, 512, 256}) {
+        int64_t n = 0;
+        double wide = 0;
+        double e = prefill_est(small, sp, true, dec_wgs, &n);
+        if (n + dec_wgs > slots) break;
+        if (dec_keys > 0) {
+          wide_split(n + app_wgs, &wide);
+          if (wide < (wave_fits ? 0.9 : 0.75) * wave_est)
+            e = std::max(e, wide);
+          else if (wave_fits)
+            e = std::max(prefill_est(small, sp, false, dec_wgs, &n), wave_est);
+          else
+            continue;
+        }
+        if (e < best) {
+          best = e;
+          tile_tokens = small;
+          split_p = sp;
+        }
       }
     }
   }
@@ -289,27 +353,39 @@ int dlfp_build_varlen_meta(const dlfp_dims* dims, const dlfp_tuning* tuning, int
   // re-reads its keys and values more often but merges fewer bytes per row
   // group).  So the tallest tile of 128, 64 or 32 rows whose units, with the
   // shortest split of at least 1024 keys that keeps them at most one per
-  // compute unit, come within 1/16 of that count; else 32 rows.  (Measured on
+  // compute unit, come within 1/16 of that count; else 32 rows.  When a lower tile has more units
+  // than that even whole, its few very long units are the launch: then 128 rows
+  // and up to one and a half units per compute unit (g = 8, 176 tokens over
+  // 9871 beside 24 decoders: 352 units of 9856 keys of 32-row tiles 166 us, as
+  // many of 2560 keys of 128-row tiles 86 us; g = 2, 1082 over 10784 beside 61:
+  // 205 -> 159 us).  (Measured on
   // Qwen3-0.6B shapes beside 32 decoders: 44-48 us per layer instead of
   // 50-54 us for chunks of 64-256 tokens over prefixes of 2-6k keys.)
-  const bool has_decode = dec_keys > 0;
-  if (!split_p && !tn.prefill_tile_tokens && pre_keys > 0 && has_decode) {
+  if (!split_p && !tn.prefill_tile_tokens && pre_keys > 0 && dec_keys > 0) {
     const int64_t target = std::max<int64_t>(1, resident / 8);
-    for (int rows : {DLFP_TILE_ROWS, DLFP_TILE_ROWS / 2, DLFP_TILE_ROWS / 4}) {
-      const int64_t tt = std::max(1, rows / g);
-      // The shortest split of 1024 + 64 k keys keeping the units within the
-      // target (DLFP_MAX_PREFILL_UNIT_KEYS when none does), by bisection: the
-      // unit count only falls as the split grows.
+    // The shortest split of 1024 + 64 k keys keeping the units within `most`
+    // (DLFP_MAX_PREFILL_UNIT_KEYS when none does), by bisection: the unit
+    // count only falls as the split grows.
+    auto shortest = [&](int64_t tt, int64_t most) {
       int64_t lo = 0, hi = (DLFP_MAX_PREFILL_UNIT_KEYS - 1024) / 64;
       while (lo < hi) {
         const int64_t mid = (lo + hi) / 2;
-        if (prefill_units(tt, 1024 + 64 * mid) > target)
+        if (prefill_units(tt, 1024 + 64 * mid) > most)
           lo = mid + 1;
         else
           hi = mid;
       }
-      const int64_t sp = 1024 + 64 * lo;
-      if (prefill_units(tt, sp) * 16 >= target * 15 || rows == DLFP_TILE_ROWS / 4) {
+      return 1024 + 64 * lo;
+    };
+    for (int rows : {DLFP_TILE_ROWS, DLFP_TILE_ROWS / 2, DLFP_TILE_ROWS / 4}) {
+      const int64_t tt = std::max(1, rows / g);
+      const int64_t sp = shortest(tt, target), n = prefill_units(tt, sp);
+      if (n > target && rows != DLFP_TILE_ROWS) {  // too many even whole
+        tile_tokens = std::max(1, DLFP_TILE_ROWS / g);
+        split_p = shortest(tile_tokens, target + target / 2);
+        break;
+      }
+      if (n * 16 >= target * 15 || rows == DLFP_TILE_ROWS / 4) {
         tile_tokens = (int)tt;
         split_p = sp;
         break;
@@ -343,27 +419,31 @@ int dlfp_build_varlen_meta(const dlfp_dims* dims, const dlfp_tuning* tuning, int
       if (sp >= max_kend || sp >= DLFP_MAX_PREFILL_UNIT_KEYS) break;
     }
   }
+  // Decode units of a workgroup beside the prefill units where their estimate
+  // is clearly the lower one and, beside tall tiles, the decode share is not
+  // hidden behind them anyway: more workgroups then only crowd the tiles (11
+  // decoders of 38-304 keys beside 796 tokens over 858, g = 2: 34.6 against
+  // 35.4 us; 6 of 796-6368 beside 321 over 1359: 40.1 against 33.3 us; 30 of
+  // 906-7248 beside 20 tokens, g = 4, where they do not fit well: 85.2 against
+  // 93.8 us).
+  const bool tall = tile_tokens * g > 32;
+  int64_t pre_units = 0;
+  const double pre_est = prefill_est(tile_tokens, split_p, !tall, 0, &pre_units);
   int64_t split_d = tn.decode_split_tokens;
   if (!split_d) {
-    int64_t pre_units = 0;
-    for (int s = 0; s < num_seqs; ++s) {
-      if (q_len[s] == 1) continue;
-      const int64_t pos0 = kv_len[s] - q_len[s];
-      for (int64_t t0 = 0; t0 < q_len[s]; t0 += tile_tokens) {
-        const int64_t nt = std::min<int64_t>(tile_tokens, q_len[s] - t0);
-        pre_units += hkv * ceil_div(pos0 + t0 + nt, split_p);
-      }
-    }
-    // The decode share starts in the workgroup slots (two per CU, four
-    // wavefronts each) that the prefill units leave, at least 64; when the
-    // prefill units take them all, it runs as they retire.
-    split_d = pre_units == 0
-                  ? wide_split()
+    double wide = 0;
+    const int64_t sd = wide_split(pre_units > 0 ? pre_units + app_wgs : 0, &wide);
+    const bool use_wide =
+        pre_units == 0 || (wide < 0.9 * wave_est && (!tall || wave_est > 0.5 * pre_est));
+    // As wavefront units the decode share starts in the workgroup slots (two
+    // per CU, four wavefronts each) that the prefill units leave, at least 64;
+    // when the prefill units take them all, it runs as they retire.
+    split_d = use_wide
+                  ? sd
                   : decode_split(pre_units < resident / 4
                                      ? std::max<int64_t>(resident / 4 - pre_units, 64)
                                      : resident / 4);
   }
-
   // Build units: prefill (KV-head-major), then decode.  Capacity: every key
   // range is cut into at most ceil(range / split) parts, plus two tail pieces.
   std::vector<Unit> units;
@@ -425,6 +505,8 @@ int dlfp_build_varlen_meta(const dlfp_dims* dims, const dlfp_tuning* tuning, int
       u.f[DLFP_W_KIND] = kind;
       u.f[DLFP_W_QROW0] = (int32_t)(cu_q_of[s] + t0);
       u.f[DLFP_W_QPOS0] = (int32_t)(kv_len[s] - q_len[s] + t0);
+      if (kind == DLFP_KIND_PREFILL)
+        u.f[DLFP_W_PAGE0] = !tall;
       if (kind == DLFP_KIND_DECODE) {
         // The unit's first two block ids travel with the record, so its first
         // page loads go out with its query and block-table loads.

@@ -437,3 +437,51 @@ def test_decode_only_many_units(dev, ws, g):
     torch.cuda.synchronize()
     assert not ws.buf[:D.WORKSPACE_PARTIALS].view(torch.int32).cpu().numpy().any()
     _compare(_to64(out), seqs, f"many wide units g={g}")
+
+
+# (new tokens, context): prompts without a prefix, one that starts inside a page, at a page
+# and at a 32-key block, chunks of one tile, of several and of a partly filled last one; and
+# decoders beside them.
+SMALL_PROMPTS = [(2, 2), (5, 38), (17, 49), (33, 129), (20, 500)]
+SMALL_DECODERS = [(1, 1), (1, 17), (1, 260), (1, 1100)]
+
+
+@pytest.mark.parametrize("g,hkv,specs,split,tile,fused", [
+    (1, 2, SMALL_PROMPTS + SMALL_DECODERS, 0, 0, True),
+    (2, 4, SMALL_PROMPTS + SMALL_DECODERS, 64, 16, True),
+    (4, 2, SMALL_PROMPTS, 0, 0, True),
+    (4, 4, SMALL_PROMPTS, 128, 3, False),
+    (8, 2, SMALL_PROMPTS + SMALL_DECODERS, 192, 0, False),
+    (8, 1, SMALL_PROMPTS + SMALL_DECODERS, 0, 1, True),
+    # append records in a launch of their own
+    (2, 4, [(300, 561), (250, 250)] + SMALL_DECODERS, 0, 16, True),
+])
+def test_small_prefill_units(dev, ws, g, hkv, specs, split, tile, fused):
+    """Prefill units of at most 32 rows, alone and beside decode units of a
+    workgroup: the records carry the flag, whole ranges and splits agree with the
+    oracle with every unwritten slot NaN, the cache gets the new tokens, the
+    workspace words are zero again."""
+    shape = wl.AttnShape(g * hkv, hkv)
+    seqs = _seqs(shape, specs, seed=90 + g + split)
+    tuning = D.dlfp_tuning(0, split, 0, tile if tile or not split else 32 // g)
+    it = rt.Iteration(D.make_dims(g * hkv, hkv), seqs, _pool_for(seqs), 11, dev,
+                      fill_bits=rt.BF16_NAN_BITS, tuning=tuning)
+    m = it.batch.meta
+    assert (m.records[:m.num_prefill_units, 14] == 1).all()  # DLFP_W_PAGE0
+    if len(specs) > len(SMALL_PROMPTS):
+        assert m.num_units <= 512 - 16 and m.decode_split_tokens > 128
+    two = rt.Iteration(D.make_dims(g * hkv, hkv), seqs, _pool_for(seqs), 11, dev,
+                       fill_bits=rt.BF16_NAN_BITS, tuning=tuning)
+    outs = []
+    for _ in range(2):  # the second launch relies on the words the first left
+        outs.append(torch.full((sum(q for q, _ in specs), g * hkv, 128), float("nan"),
+                               dtype=torch.float32, device=dev))
+        it.run(ws, SCALE, out=outs[-1], fused=fused)
+    outs.append(two.run(ws, SCALE, torch.float32, fused=False))
+    torch.cuda.synchronize()
+    assert torch.equal(outs[0], outs[1]) and torch.equal(outs[0], outs[2])
+    assert D.dlfp_workspace_error(ws.buf) == 0
+    assert not ws.buf[:D.WORKSPACE_PARTIALS].view(torch.int32).cpu().numpy().any()
+    assert torch.equal(it.pool.k.view(torch.int16), two.pool.k.view(torch.int16))
+    assert torch.equal(it.pool.v.view(torch.int16), two.pool.v.view(torch.int16))
+    _compare(_to64(outs[0]), seqs, f"small prefill g={g} hkv={hkv} split={split} tile={tile}")
