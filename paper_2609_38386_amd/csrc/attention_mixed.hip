@@ -384,6 +384,20 @@ __device__ __forceinline__ void lds_copy16(const char* src, uint32_t lds) {
                : "v"(src), "s"(lds)
                : "memory", "m0");
 }
+// The same copy from a wave-uniform base and a lane's byte offset (the address
+// costs no vector instruction).
+__device__ __forceinline__ const char* uniform_ptr(const void* p) {
+  const uint64_t v = reinterpret_cast<uint64_t>(p);
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
+  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
+  return reinterpret_cast<const char*>(((uint64_t)hi << 32) | lo);
+}
+__device__ __forceinline__ void lds_copy16(const char* base, uint32_t off, uint32_t lds) {
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
+               :
+               : "v"(off), "s"(base), "s"(lds)
+               : "memory", "m0");
+}
 // The same copy marked non-temporal, for the decode share's pages: each is
 // read once per launch, so streaming them past the caches keeps the prefill
 // share's K/V tiles (read by many query tiles) resident in L2 and raises the
@@ -478,7 +492,7 @@ __device__ __forceinline__ void prefill_merge(const Args& a, const Slots sl, int
   }
 }
 
-// MIXED: the launch also has decode units (the QK products' issue order below).
+// MIXED: the launch also has decode units (the issue order of the tile loop).
 template <int G, bool APP, bool MIXED, class R>
 __device__ void prefill_unit(const Args& a, const int32_t* it, const R f, char* smem, int* flag) {
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
@@ -538,25 +552,28 @@ __device__ void prefill_unit(const Args& a, const int32_t* it, const R f, char* 
   // Straight-line on purpose: a page past the unit's last key re-reads its
   // last page (every key there is masked), and a block id outside the pool is
   // replaced by block 0 after raising the error word.
-  // Element offset of this wave's page of tile t (same in both caches).
-  auto page_off = [&](int t) -> int64_t {
-    const int page = min(first_page + 4 * t + wave, last_page);
-    const int raw = uniform(ptab[page - first_page]);
+  // Block id of this wave's page of tile t, and its element offset (same in
+  // both caches).
+  auto page_id = [&](int t) {
+    return ptab[min(first_page + 4 * t + wave, last_page) - first_page];
+  };
+  auto page_off = [&](int id) -> int64_t {
+    const int raw = uniform(id);
     const bool ok = (unsigned)raw < (unsigned)a.num_blocks;
     if (!ok && lane == 0) raise_error(a.ws);
     return ((int64_t)(ok ? raw : 0) * a.hkv + kh) * PAGE_ELEMS;
   };
   const uint32_t lds_wave = lds_addr(smem) + uniform(wave) * (PAGE * 256);
   auto issue_k = [&](int64_t off, int slot) {
-    const char* src = reinterpret_cast<const char*>(a.kc + off);
+    const char* src = uniform_ptr(a.kc + off);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) lds_copy16(src + koff[i], lds_wave + slot * TILE_BYTES + i * 1024);
+    for (int i = 0; i < 4; ++i) lds_copy16(src, koff[i], lds_wave + slot * TILE_BYTES + i * 1024);
   };
   auto issue_v = [&](int64_t off, int slot) {
-    const char* src = reinterpret_cast<const char*>(a.vc + off);
+    const char* src = uniform_ptr(a.vc + off);
 #pragma unroll
     for (int i = 0; i < 4; ++i)
-      lds_copy16(src + voff[i], lds_wave + V_BASE + slot * TILE_BYTES + i * 1024);
+      lds_copy16(src, voff[i], lds_wave + V_BASE + slot * TILE_BYTES + i * 1024);
   };
   // Values past the unit's last key are zeroed in LDS (a probability of 0
   // times a NaN left in an unused slot would still be NaN).
@@ -610,19 +627,31 @@ __device__ void prefill_unit(const Args& a, const int32_t* it, const R f, char* 
         sacc[kb2][rr] = key < lim ? sacc[kb2][rr] : -__builtin_inff();
       }
   };
-  // Row maximum of a tile (raw scores), both halves of the row.
+  // Row maximum of a tile (raw scores), this half of the row; in four chains
+  // where the products do not wait for anything else (beside decode wavefronts
+  // one chain is 0.5% faster).
   auto rowmax = [&](const f32x16_t* sacc) {
-    float mx = -__builtin_inff();
+    if constexpr (MIXED) {
+      float mx = -__builtin_inff();
 #pragma unroll
-    for (int kb2 = 0; kb2 < 2; ++kb2)
+      for (int i = 0; i < 32; ++i) mx = fmaxf(mx, sacc[i >> 4][i & 15]);
+      return mx;
+    }
+    float m4[4];
 #pragma unroll
-      for (int rr = 0; rr < 16; ++rr) mx = fmaxf(mx, sacc[kb2][rr]);
-    return max_xor32(mx);
+    for (int i = 0; i < 4; ++i)
+      m4[i] = fmaxf(sacc[i >> 1][8 * (i & 1)], sacc[i >> 1][8 * (i & 1) + 1]);
+#pragma unroll
+    for (int rr = 2; rr < 8; ++rr)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) m4[i] = fmaxf(m4[i], sacc[i >> 1][8 * (i & 1) + rr]);
+    return fmaxf(fmaxf(m4[0], m4[1]), fmaxf(m4[2], m4[3]));
   };
-  // Raise the reference maximum where a tile exceeds it by more than
-  // RESCALE_LOG2 (scaled units); the accumulators follow.
+  // Raise the reference maximum where a tile's row maximum (mx: of one half of
+  // the row) exceeds it by more than RESCALE_LOG2 (scaled units); the
+  // accumulators follow.
   auto rebase = [&](float mx) {
-    const float m_tile = mx * c;
+    const float m_tile = max_xor32(mx) * c;
     if (__builtin_amdgcn_ballot_w64(m_tile > m_run + RESCALE_LOG2)) {
       const float m_new = m_tile > m_run + RESCALE_LOG2 ? m_tile : m_run;
       const float alpha = fexp2(m_run - m_new);
@@ -633,10 +662,10 @@ __device__ void prefill_unit(const Args& a, const int32_t* it, const R f, char* 
     }
   };
   // P^T = exp2(S^T c - m) rounded to bf16, as the B operands of the four
-  // 16-key steps of PV; pf[kk] holds keys 16 kk + {0-3, 8-11} + 4 hi.
-  auto probs = [&](const f32x16_t* sacc, bf16x8_t* pf) {
+  // 16-key steps k0 .. k1 - 1 of PV; pf[kk] holds keys 16 kk + {0-3, 8-11} + 4 hi.
+  auto probs = [&](const f32x16_t* sacc, bf16x8_t* pf, int k0, int k1) {
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk) {
+    for (int kk = k0; kk < k1; ++kk) {
       u32x4_t pk;
 #pragma unroll
       for (int w = 0; w < 4; ++w) {
@@ -657,10 +686,10 @@ __device__ void prefill_unit(const Args& a, const int32_t* it, const R f, char* 
       for (int w = 0; w < 4; ++w) l_run = dot2(pk[w], ONES, l_run);
     }
   };
-  // O^T += V^T P^T over the tile in V slot `slot`.
-  auto pv = [&](const bf16x8_t* pf, int slot) {
+  // O^T += V^T P^T over the 16-key steps k0 .. k1 - 1 of the tile in V slot `slot`.
+  auto pv = [&](const bf16x8_t* pf, int slot, int k0, int k1) {
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk)
+    for (int kk = k0; kk < k1; ++kk)
 #pragma unroll
       for (int mb = 0; mb < 4; ++mb) {
         const bf16x8_t vf = *reinterpret_cast<const bf16x8_t*>(
@@ -680,11 +709,11 @@ __device__ void prefill_unit(const Args& a, const int32_t* it, const R f, char* 
   if constexpr (APP) {
     if (wait_tile <= 1) wait_for_appends(a);
   }
-  int64_t off_next = page_off(0);
+  int64_t off_next = page_off(page_id(0));
   issue_k(off_next, 0);
   issue_v(off_next, 0);
   if (ntiles > 1) {
-    off_next = page_off(1);
+    off_next = page_off(page_id(1));
     issue_k(off_next, 1);
   }
   wait_memory_complete();
@@ -700,67 +729,89 @@ __device__ void prefill_unit(const Args& a, const int32_t* it, const R f, char* 
     rebase(rowmax(sa));
   }
   __syncthreads();  // K slot 0 is refilled below
+  int id2 = page_id(2);  // read a step before its use
 
   // Iteration j: loads of K_{j+2} and V_{j+1} go out; S_{j+1} = K_{j+1} Q^T
-  // runs on the matrix cores while the probabilities of tile j are formed;
-  // then O += V_j P_j runs while the row maxima of tile j + 1 are taken.
+  // runs on the matrix cores while probabilities of tile j are formed (without
+  // decode units the first half of them, the second half beside the first half
+  // of O += V_j P_j, and the row maxima of tile j + 1 beside its second half:
+  // the exponentials outlast the QK products); then O += V_j P_j.  Large
+  // launches are bound by the clock the power limit leaves (1.7 of 2.4 GHz).
+  // With that order, the addresses of the copies in scalar registers and the
+  // block ids read a step ahead: prefill alone, 2048 tokens over 6144 keys
+  // (g = 2) 131.6 -> 128.2 us, 4096 over 8192 (g = 8) 1192 -> 1157 us; beside decode
+  // units, in their order, 8192 tokens over 16384 6727 -> 6587 us.
   auto step = [&](int j, f32x16_t* cur, f32x16_t* nxt, auto parity) {
     constexpr int PAR = decltype(parity)::value;  // j & 1
+    constexpr int FIRST = MIXED ? 4 : 2;  // 16-key steps whose exponentials run beside QK
     const bool more = j + 1 < ntiles;
     if (more) issue_v(off_next, PAR ^ 1);
     if (j + 2 < ntiles) {
-      off_next = page_off(j + 2);
+      off_next = page_off(id2);
       issue_k(off_next, PAR);
     }
+    id2 = page_id(j + 3);
     if (wave_active) {
       bf16x8_t pf[4];
       // On the last tile this reads a stale slot; the result is not used, and
       // keeping it unconditional lets the products overlap the exponentials.
       qk(nxt, PAR ^ 1);
-      probs(cur, pf);
-      // Beside decode workgroups a prefill wavefront has no second prefill
-      // wavefront on its SIMD to overlap with, so in a mixed launch the key
-      // operands of the QK products are read four products ahead, one per
-      // product, and the exponentials fill the gaps between the products.
-      // Beside prefill wavefronts the compiler's own order is faster
-      // (measured: Qwen3-32B sweep 0.8% faster with this order in mixed
-      // launches, prefill-only launches 0.6-1% slower with it).
-      if constexpr (MIXED) {
-        __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
+      probs(cur, pf, 0, FIRST);
+      // The key operands of the QK products are read four products ahead, one
+      // per product, and the exponentials fill the gaps between the products.
+      __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-          __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-        }
+      for (int i = 0; i < 16; ++i) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
       }
       // The PV products and row sums run at raised wave priority: the SIMD
       // arbiter then keeps feeding the matrix core of the wave that is past
       // its exponentials while the other waves of the CU finish theirs
       // (measured 4-7% more prefill throughput on long chunks).
       __builtin_amdgcn_s_setprio(1);
-      pv(pf, PAR);
-      rowsum(pf);
       // Issue order of the raised-priority phase (s_setprio ends a scheduling
-      // region, so these groups order the PV(j) products, the LDS reads of
-      // their value operands and the row sums only).
-      __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
+      // region): the value operands four products ahead, VALU work between.
+      float mx;
+      if constexpr (MIXED) {
+        pv(pf, PAR, 0, 4);
+        rowsum(pf);
+        __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
 #pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-        __builtin_amdgcn_sched_group_barrier(0x002, 6, 0);
-        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-      }
+        for (int i = 0; i < 16; ++i) {
+          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+          __builtin_amdgcn_sched_group_barrier(0x002, 6, 0);
+          __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+        }
+      } else {
+        probs(cur, pf, FIRST, 4);
+        pv(pf, PAR, 0, FIRST);
+        __builtin_amdgcn_sched_group_barrier(0x100, 4, 1);
 #pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-        __builtin_amdgcn_sched_group_barrier(0x002, 1, 0);
-        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+        for (int i = 0; i < 4 * FIRST; ++i) {
+          __builtin_amdgcn_sched_group_barrier(0x008, 1, 1);
+          __builtin_amdgcn_sched_group_barrier(0x002, 5, 1);
+          __builtin_amdgcn_sched_group_barrier(0x100, 1, 1);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        pv(pf, PAR, FIRST, 4);
+        rowsum(pf);
+        mx = rowmax(nxt);
+        __builtin_amdgcn_sched_group_barrier(0x100, 4, 2);
+#pragma unroll
+        for (int i = 0; i < 16 - 4 * FIRST; ++i) {
+          __builtin_amdgcn_sched_group_barrier(0x008, 1, 2);
+          __builtin_amdgcn_sched_group_barrier(0x002, 5, 2);
+          __builtin_amdgcn_sched_group_barrier(0x100, 1, 2);
+        }
       }
       __builtin_amdgcn_s_setprio(0);
       if (more) {
         const int k1 = kb + (j + 1) * KV_TILE;
-        if (k1 + KV_TILE > wave_lim_min) mask(nxt, k1);
-        rebase(rowmax(nxt));
+        const bool masked = k1 + KV_TILE > wave_lim_min;
+        if (masked) mask(nxt, k1);
+        if (MIXED || masked) mx = rowmax(nxt);
+        rebase(mx);
       }
     }
     wait_memory_complete();
