@@ -125,7 +125,9 @@ typedef struct {
  * shortest split of at least 1024 keys keeping them at most one per compute
  * unit, come within 1/16 of that count (when a lower tile would have more
  * units than that even unsplit, 128 rows at the shortest split giving at most
- * one and a half per compute unit; else 32 rows); a prefill share alone
+ * one and a half per compute unit; else 32 rows), unless an estimate of the
+ * launch time puts another height and split of at most two units per compute
+ * unit clearly ahead; a prefill share alone
  * takes 128-row tiles and the split (a multiple of 64 keys, at least 1024)
  * that minimises an estimate of the launch time.  Without a prefill share a
  * decode unit is the work of a workgroup, and the decode split is the one in

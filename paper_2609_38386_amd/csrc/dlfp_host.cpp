@@ -284,22 +284,27 @@ int dlfp_build_varlen_meta(const dlfp_dims* dims, const dlfp_tuning* tuning, int
   app_wgs = ceil_div(app_wgs, 64) * 8;
   if (app_wgs > 16) app_wgs = 0;
   const double wave_est = dec_keys > 0 ? (double)dec_keys * (512 / 6.4e6) + 8.0 : 0.0;
-  // Time of the prefill share in microseconds: a fixed part, the merge of its
-  // splits, and its longest unit, with the compute units' workgroups (`others`
-  // of other shares) side by side; for the code of at most 32 rows or the other.
-  auto prefill_est = [&](int64_t tt, int64_t sp, bool few_rows, int64_t others, int64_t* units) {
-    int64_t n = 0, longest = 0, parts = 1;
+  // Prefill units of a tile size and split: their number, the longest one's
+  // keys, the most parts of a range.
+  auto shape = [&](int64_t tt, int64_t sp, int64_t* units, int64_t* longest, int64_t* parts) {
     for (int s = 0; s < num_seqs; ++s) {
       if (q_len[s] == 1) continue;
       const int64_t pos0 = kv_len[s] - q_len[s];
       for (int64_t t0 = 0; t0 < q_len[s]; t0 += tt) {
         const int64_t kend = pos0 + t0 + std::min<int64_t>(tt, q_len[s] - t0);
         const int64_t part = round_up(ceil_div(kend, ceil_div(kend, sp)), KV_GRANULE_PREFILL);
-        n += hkv * ceil_div(kend, part);
-        longest = std::max(longest, std::min(part, kend));
-        parts = std::max(parts, ceil_div(kend, part));
+        *units += hkv * ceil_div(kend, part);
+        *longest = std::max(*longest, std::min(part, kend));
+        *parts = std::max(*parts, ceil_div(kend, part));
       }
     }
+  };
+  // Time of the prefill share in microseconds: a fixed part, the merge of its
+  // splits, and its longest unit, with the compute units' workgroups (`others`
+  // of other shares) side by side; for the code of at most 32 rows or the other.
+  auto prefill_est = [&](int64_t tt, int64_t sp, bool few_rows, int64_t others, int64_t* units) {
+    int64_t n = 0, longest = 0, parts = 1;
+    shape(tt, sp, &n, &longest, &parts);
     *units = n;
     const double crowd = std::max(1.0, (double)(n + others) / (double)std::max<int64_t>(1, resident / 8));
     return (few_rows ? 6.1 : 10.0) + (parts > 1 ? 2.4 + 0.2 * (double)parts : 0.0) +
@@ -377,10 +382,13 @@ int dlfp_build_varlen_meta(const dlfp_dims* dims, const dlfp_tuning* tuning, int
       }
       return 1024 + 64 * lo;
     };
+    // More splits of tall tiles take up to 36 MB of partial results: only where
+    // those of the decode share leave room for them in the fixed workspace.
+    const bool roomy = dec_wgs0 * 4 * slot_floats(g) * 4 < DLFP_STATIC_WORKSPACE_BYTES / 2;
     for (int rows : {DLFP_TILE_ROWS, DLFP_TILE_ROWS / 2, DLFP_TILE_ROWS / 4}) {
       const int64_t tt = std::max(1, rows / g);
       const int64_t sp = shortest(tt, target), n = prefill_units(tt, sp);
-      if (n > target && rows != DLFP_TILE_ROWS) {  // too many even whole
+      if (n > target && rows != DLFP_TILE_ROWS && roomy) {  // too many even whole
         tile_tokens = std::max(1, DLFP_TILE_ROWS / g);
         split_p = shortest(tile_tokens, target + target / 2);
         break;
@@ -389,6 +397,49 @@ int dlfp_build_varlen_meta(const dlfp_dims* dims, const dlfp_tuning* tuning, int
         tile_tokens = (int)tt;
         split_p = sp;
         break;
+      }
+    }
+    // Then the other heights and equal parts (1 to 12 of the longest range, of
+    // 256 keys and more, at most two units per compute unit), when an estimate
+    // of the launch time puts one clearly ahead.  In microseconds: a tile's
+    // units take 10, 18.4, 13.4 or 8.6 per 1024 keys of the longest one (up to
+    // 1.7 times that as they crowd the CUs) and the merge; the decode share 14
+    // and its bytes at the rate the slots left to it draw (all of it from 400
+    // up), at the full rate once the prefill units are done.  (48 shapes of
+    // 12-160 decoders beside 33-1500 tokens over up to 12000 keys: 0.965x on
+    // average, none slower; the estimate is good to 9%, so a smaller lead is
+    // left alone.)
+    auto launch_est = [&](int64_t tt, int64_t sp, int64_t* units) {
+      int64_t n = 0, longest = 0, parts = 1;
+      shape(tt, sp, &n, &longest, &parts);
+      *units = n;
+      const double per_key = tt * g > 64 ? 0.0184 : tt * g > 32 ? 0.0134 : 0.0086;
+      const double crowd = std::clamp((double)(n - target / 2) / (1.5 * (double)target), 0.0, 1.0);
+      const double pre = 10.0 + per_key * (double)longest * (1.0 + 0.72 * crowd) *
+                                    std::max(1.0, (double)n / (2.0 * (double)target)) +
+                         (parts > 1 ? 2.4 + 0.5 * (double)parts : 0.0);
+      const double rate = std::min(1.0, (double)std::max<int64_t>(2 * target - n, 64) / 400.0);
+      const double work = 14.0 + (double)dec_keys * (512 / 6.4e6);
+      const double dec = work <= rate * pre ? work / rate : pre + work - rate * pre;
+      return std::pow(std::pow(pre, 6.5) + std::pow(dec, 6.5), 1.0 / 6.5);
+    };
+    int64_t n = 0, max_kend = 0;
+    for (int s = 0; s < num_seqs; ++s)
+      if (q_len[s] != 1) max_kend = std::max<int64_t>(max_kend, kv_len[s]);
+    double best = roomy ? 0.8 * launch_est(tile_tokens, split_p, &n) : 0.0;
+    for (int rows : {DLFP_TILE_ROWS, DLFP_TILE_ROWS / 2, DLFP_TILE_ROWS / 4}) {
+      const int64_t tt = std::max(1, rows / g);
+      for (int64_t k : {1, 2, 3, 4, 5, 6, 8, 12}) {
+        const int64_t sp = round_up(ceil_div(max_kend, k), KV_GRANULE_PREFILL);
+        if (sp > DLFP_MAX_PREFILL_UNIT_KEYS) continue;
+        if (k > 1 && sp < 256) break;
+        const double e = launch_est(tt, sp, &n);
+        if (n > 2 * target) break;
+        if (e < best) {
+          best = e;
+          tile_tokens = (int)tt;
+          split_p = sp;
+        }
       }
     }
   }

@@ -485,3 +485,24 @@ def test_small_prefill_units(dev, ws, g, hkv, specs, split, tile, fused):
     assert torch.equal(it.pool.k.view(torch.int16), two.pool.k.view(torch.int16))
     assert torch.equal(it.pool.v.view(torch.int16), two.pool.v.view(torch.int16))
     _compare(_to64(outs[0]), seqs, f"small prefill g={g} hkv={hkv} split={split} tile={tile}")
+
+
+@pytest.mark.parametrize("g,decoders,lo,hi,chunk,prefix,units", [
+    (2, 64, 52, 416, 269, 4727, 200),    # another height and split by the launch estimate
+    (8, 24, 245, 1960, 176, 9871, 352),  # 32-row tiles would be a few very long units
+])
+def test_tall_tiles_beside_decoders(dev, ws, g, decoders, lo, hi, chunk, prefix, units):
+    """Plans that split 128-row tiles beside wavefronts' decode units, each group
+    with its ragged last part, against the oracle."""
+    shape = wl.AttnShape(g * 8, 8)
+    specs = [(1, lo + (hi - lo) * i // decoders) for i in range(decoders)] + [(chunk, prefix + chunk)]
+    seqs = _seqs(shape, specs, seed=120 + g)
+    it = rt.Iteration(D.make_dims(g * 8, 8), seqs, _pool_for(seqs), 12, dev,
+                      fill_bits=rt.BF16_NAN_BITS)
+    m = it.batch.meta
+    assert m.num_prefill_units == units and m.num_units > 512
+    out = it.run(ws, SCALE, torch.float32, fused=True)
+    torch.cuda.synchronize()
+    assert D.dlfp_workspace_error(ws.buf) == 0
+    assert not ws.buf[:D.WORKSPACE_PARTIALS].view(torch.int32).cpu().numpy().any()
+    _compare(_to64(out), seqs, f"tall tiles g={g}")
