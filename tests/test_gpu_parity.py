@@ -506,3 +506,34 @@ def test_tall_tiles_beside_decoders(dev, ws, g, decoders, lo, hi, chunk, prefix,
     assert D.dlfp_workspace_error(ws.buf) == 0
     assert not ws.buf[:D.WORKSPACE_PARTIALS].view(torch.int32).cpu().numpy().any()
     _compare(_to64(out), seqs, f"tall tiles g={g}")
+
+
+@pytest.mark.parametrize("case", ["aligned", "offset", "ragged", "broken", "edge"])
+def test_kv_append_pages_anywhere(dev, case):
+    """Pages that begin anywhere in a block of 16 packed tokens, pages cut short by
+    the end of a run, of the tokens or of the pool, slots out of order, left out
+    (negative) or outside the pool: every slot's bits, and no other's, change."""
+    rng = np.random.default_rng(130)
+    hkv, blocks, page = 3, 40, D.PAGE_SIZE
+    def runs(*spans):
+        return np.concatenate([np.arange(a, a + n) for a, n in spans])
+    slots = {"aligned": runs((32, 64)),
+             "offset": runs((67, 150)),
+             "ragged": runs((5, 1), (17, 33), (100, 47), (208, 16), (240, 15), (300, 40), (351, 1)),
+             "broken": np.concatenate([runs((64, 16))[::-1], runs((80, 40)), [-1, -5], runs((130, 33)),
+                                       runs((176, 8)), runs((185, 20)), [640, 10 ** 6], runs((224, 16))]),
+             "edge": runs((601, 39), (640, 9))}[case].astype(np.int32)
+    n = len(slots)
+    k = rng.integers(0, 1 << 16, (n, hkv, 128), dtype=np.uint16)
+    v = rng.integers(0, 1 << 16, (n, hkv, 128), dtype=np.uint16)
+    pool = rt.KVPool(blocks, hkv, dev, rt.BF16_NAN_BITS)
+    want_k, want_v = (x.copy() for x in pool.host_bits())
+    for i, s in enumerate(slots):
+        if 0 <= s < blocks * page:
+            t = s % page
+            want_k[s // page, :, t, :] = k[i]
+            want_v[s // page, :, :, (t & 3) | ((t & 4) << 1) | ((t & 8) >> 1)] = v[i]
+    D.dlfp_kv_append(D.make_dims(hkv, hkv), rt.bits_to_device(k, dev), rt.bits_to_device(v, dev),
+                     torch.from_numpy(slots).to(dev), pool.k, pool.v)
+    got_k, got_v = pool.host_bits()
+    assert np.array_equal(got_k, want_k) and np.array_equal(got_v, want_v)
