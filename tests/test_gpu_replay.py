@@ -8,6 +8,7 @@ import torch
 
 from oracle import controller as oc
 from paper_2609_38386_amd import replay as rp
+from paper_2609_38386_amd import workload as wl
 
 pytestmark = pytest.mark.gpu
 
@@ -79,12 +80,16 @@ def test_gpu_retimed_layer_leaves_the_same_state():
     """An iteration whose enqueue outlasts the stream hold is timed a second
     time; its launches are idempotent, so the pages and outputs after a replay
     in which every iteration is timed twice (a 1 us hold) equal, bit for bit,
-    those of a replay timed once per iteration.  Uncapped decisions do not
-    depend on the measured latencies, so both replays run the same batches."""
+    those of a replay timed once per iteration.  Uncapped decisions depend on
+    the measured latencies only through the requests that have arrived when an
+    iteration ends; here all have when the first does, so both replays run the
+    same batches: they arrive within 9 us of the start, and an iteration takes at
+    least 28 layers x 7 launches, each after the one before, of 1 us each."""
     assert torch.cuda.is_available()
     dev = torch.device("cuda:0")
-    cfg = rp.ReplayConfig(seed=804, n_requests=5, rate_per_s=400.0, prompt_hi=1536, out_len=6,
+    cfg = rp.ReplayConfig(seed=804, n_requests=5, rate_per_s=1.0e6, prompt_hi=1536, out_len=6,
                           layer_proxy=True)
+    assert wl.poisson_arrivals(cfg.seed, cfg.n_requests, cfg.rate_per_s)[-1] < 9e-6 < 28 * 7e-6
     once, twice = rp.GpuExecutor(cfg, dev), rp.GpuExecutor(cfg, dev)
     twice.hold_us = 1
     t1, t2 = [], []
