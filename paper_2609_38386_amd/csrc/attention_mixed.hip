@@ -1594,8 +1594,8 @@ __device__ int decode_unit(const Args& a, const int32_t* it_g, char* wl, bool ta
   return ticket_v;
 }
 
-// Decode unit of a whole workgroup ("wide": launches without prefill units).
-// Wavefront w takes the unit's 32-key blocks (two
+// Decode unit of a whole workgroup ("wide": launches without prefill units, and
+// those whose workgroups are all resident at once).  Wavefront w takes the unit's 32-key blocks (two
 // pages) w, w + NW, ..., so all finish together and the unit's partial results
 // meet in LDS; only units of 4096 keys and more are still merged across
 // workgroups.  Against one unit per wavefront (each of the four then merged
