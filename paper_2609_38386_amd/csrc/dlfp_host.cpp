@@ -248,10 +248,12 @@ int dlfp_build_varlen_meta(const dlfp_dims* dims, const dlfp_tuning* tuning, int
     return best_sp;
   };
   // Prefill units of the iteration for a tile size and key split.
+  std::vector<int> prompts;  // sequences of the prefill share
+  for (int s = 0; s < num_seqs; ++s)
+    if (q_len[s] != 1) prompts.push_back(s);
   auto prefill_units = [&](int64_t tt, int64_t split) {
     int64_t n = 0;
-    for (int s = 0; s < num_seqs; ++s) {
-      if (q_len[s] == 1) continue;
+    for (int s : prompts) {
       const int64_t pos0 = kv_len[s] - q_len[s];
       for (int64_t t0 = 0; t0 < q_len[s]; t0 += tt)
         n += hkv * ceil_div(pos0 + t0 + std::min<int64_t>(tt, q_len[s] - t0), split);
@@ -287,8 +289,7 @@ int dlfp_build_varlen_meta(const dlfp_dims* dims, const dlfp_tuning* tuning, int
   // Prefill units of a tile size and split: their number, the longest one's
   // keys, the most parts of a range.
   auto shape = [&](int64_t tt, int64_t sp, int64_t* units, int64_t* longest, int64_t* parts) {
-    for (int s = 0; s < num_seqs; ++s) {
-      if (q_len[s] == 1) continue;
+    for (int s : prompts) {
       const int64_t pos0 = kv_len[s] - q_len[s];
       for (int64_t t0 = 0; t0 < q_len[s]; t0 += tt) {
         const int64_t kend = pos0 + t0 + std::min<int64_t>(tt, q_len[s] - t0);
@@ -421,12 +422,16 @@ int dlfp_build_varlen_meta(const dlfp_dims* dims, const dlfp_tuning* tuning, int
       const double rate = std::min(1.0, (double)std::max<int64_t>(2 * target - n, 64) / 400.0);
       const double work = 14.0 + (double)dec_keys * (512 / 6.4e6);
       const double dec = work <= rate * pre ? work / rate : pre + work - rate * pre;
-      return std::pow(std::pow(pre, 6.5) + std::pow(dec, 6.5), 1.0 / 6.5);
+      // The larger, more when the other is near: the root is left out, only
+      // comparisons matter.
+      const double p3 = pre * pre * pre, d3 = dec * dec * dec;
+      return p3 * p3 + d3 * d3;
     };
     int64_t n = 0, max_kend = 0;
     for (int s = 0; s < num_seqs; ++s)
       if (q_len[s] != 1) max_kend = std::max<int64_t>(max_kend, kv_len[s]);
-    double best = roomy ? 0.8 * launch_est(tile_tokens, split_p, &n) : 0.0;
+    constexpr double AHEAD = 0.8 * 0.8 * 0.8;  // 20% ahead, in the estimate's sixth power
+    double best = roomy ? AHEAD * AHEAD * launch_est(tile_tokens, split_p, &n) : 0.0;
     for (int rows : {DLFP_TILE_ROWS, DLFP_TILE_ROWS / 2, DLFP_TILE_ROWS / 4}) {
       const int64_t tt = std::max(1, rows / g);
       for (int64_t k : {1, 2, 3, 4, 5, 6, 8, 12}) {
