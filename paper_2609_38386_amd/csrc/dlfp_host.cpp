@@ -186,7 +186,7 @@ int dlfp_build_varlen_meta(const dlfp_dims* dims, const dlfp_tuning* tuning, int
   // Decode split of a launch without prefill units: one unit per workgroup of
   // eight wavefronts, one workgroup per compute unit.  Every candidate (the
   // longest range in k equal parts, of at least 192 keys: eight wavefronts take
-  // 256 at a time) is weighed by an estimate of the launch time in
+  // 256 at a time; and the longest unit there is) is weighed by an estimate of the launch time in
   // microseconds.  Up to one unit per compute unit they all stream side by
   // side: while n units still have keys, 64 more keys of each (32 KiB) take
   // n x 32 KiB at the device's 6.4 TB/s or 32 KiB at a compute unit's 60 GB/s,
@@ -205,10 +205,10 @@ int dlfp_build_varlen_meta(const dlfp_dims* dims, const dlfp_tuning* tuning, int
     const int64_t cus = std::max<int64_t>(1, resident / 8);
     int64_t best_sp = DLFP_MAX_DECODE_UNIT_KEYS;
     double best = std::numeric_limits<double>::infinity();
-    for (int64_t k = ceil_div(std::max<int32_t>(max_kv, 1), DLFP_MAX_DECODE_UNIT_KEYS);;
-         k += std::max<int64_t>(1, k / 4)) {
-      const int64_t sp = std::min<int64_t>(std::max<int64_t>(round_up(ceil_div(max_kv, k), 32), 192),
-                                           DLFP_MAX_DECODE_UNIT_KEYS);
+    const int64_t least_parts = ceil_div(std::max<int32_t>(max_kv, 1), DLFP_MAX_DECODE_UNIT_KEYS);
+    for (int64_t k = 0;; k = k ? k + std::max<int64_t>(1, k / 4) : least_parts) {
+      const int64_t parts = k ? round_up(ceil_div(max_kv, k), 32) : DLFP_MAX_DECODE_UNIT_KEYS;
+      const int64_t sp = std::clamp<int64_t>(parts, 192, DLFP_MAX_DECODE_UNIT_KEYS);
       constexpr int STEP = 64, BUCKETS = DLFP_MAX_DECODE_UNIT_KEYS / STEP;
       int64_t units = 0, ending[BUCKETS + 1] = {0};
       int32_t longest = 0;
