@@ -211,19 +211,19 @@ int dlfp_build_varlen_meta(const dlfp_dims* dims, const dlfp_tuning* tuning, int
       const int64_t sp = std::clamp<int64_t>(parts, 192, DLFP_MAX_DECODE_UNIT_KEYS);
       constexpr int STEP = 64, BUCKETS = DLFP_MAX_DECODE_UNIT_KEYS / STEP;
       int64_t units = 0, ending[BUCKETS + 1] = {0};
-      int32_t longest = 0;
+      int64_t longest = 0;
       bool split = false;
       for (int s = 0; s < num_seqs; ++s) {
-        const int32_t kl = kv_len[s], n0 = (kl + (int32_t)sp - 1) / (int32_t)sp;
-        int32_t n = n0, part = kl;
+        const int64_t kl = kv_len[s], n0 = ceil_div(kl, sp);
+        int64_t n = n0, part = kl;
         if (n0 > 1) {
-          part = (int32_t)round_up((kl + n0 - 1) / n0, DLFP_PAGE_SIZE);
-          n = (kl + part - 1) / part;
+          part = round_up(ceil_div(kl, n0), DLFP_PAGE_SIZE);
+          n = ceil_div(kl, part);
           split = true;
         }
-        units += (int64_t)n * hkv;
+        units += n * hkv;
         longest = std::max(longest, part);
-        ending[(part + STEP - 1) / STEP] += (int64_t)n * hkv;
+        ending[ceil_div(part, STEP)] += n * hkv;
       }
       if (ahead > 0 && units > 2 * cus - ahead) break;  // a shorter split has more
       double e = split ? 2.5 : 0.0;

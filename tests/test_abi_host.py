@@ -171,6 +171,19 @@ def test_meta_empty_batch():
     assert meta.num_seqs == 0 and meta.num_units == 0 and meta.workspace_bytes >= 256
 
 
+@pytest.mark.parametrize("q", [1, 2])
+def test_meta_longest_context(q):
+    """The longest context an int32 holds (a pool of one block, repeated): the
+    split policy's arithmetic stays in range and the units cover every key."""
+    n = 2 ** 31 - 1
+    bt = np.zeros((1, n // 16 + 1), dtype=np.int32)
+    meta = D.dlfp_build_varlen_meta(D.make_dims(1, 1), [q], [n], bt, 1)
+    units = meta.work
+    assert meta.num_prefill_units == (0 if q == 1 else len(units))
+    begin, end = np.sort(units[:, 4]), np.sort(units[:, 5])
+    assert begin[0] == 0 and end[-1] == n and (begin[1:] == end[:-1]).all()
+
+
 def test_meta_errors():
     dims = D.make_dims(16, 8)
     bt = np.array([[0, 1, 2]], dtype=np.int32)
