@@ -383,9 +383,14 @@ int dlfp_build_varlen_meta(const dlfp_dims* dims, const dlfp_tuning* tuning, int
       }
       return 1024 + 64 * lo;
     };
-    // More splits of tall tiles take up to 36 MB of partial results: only where
-    // those of the decode share leave room for them in the fixed workspace.
-    const bool roomy = dec_wgs0 * 4 * slot_floats(g) * 4 < DLFP_STATIC_WORKSPACE_BYTES / 2;
+    // More splits of tall tiles take partial results of up to two units per
+    // compute unit (34 MB): only where the fixed workspace holds them beside
+    // those of the decode share.
+    const int64_t dec_bytes = dec_wgs0 * 4 * slot_floats(g) * 4;
+    const int64_t tall_bytes = 2 * target * slot_floats(DLFP_TILE_ROWS) * 4;
+    const bool roomy =
+        dec_bytes < DLFP_STATIC_WORKSPACE_BYTES / 2 &&
+        DLFP_WORKSPACE_PARTIALS + dec_bytes + tall_bytes <= DLFP_STATIC_WORKSPACE_BYTES;
     for (int rows : {DLFP_TILE_ROWS, DLFP_TILE_ROWS / 2, DLFP_TILE_ROWS / 4}) {
       const int64_t tt = std::max(1, rows / g);
       const int64_t sp = shortest(tt, target), n = prefill_units(tt, sp);

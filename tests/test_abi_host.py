@@ -184,6 +184,20 @@ def test_meta_longest_context(q):
     assert begin[0] == 0 and end[-1] == n and (begin[1:] == end[:-1]).all()
 
 
+@pytest.mark.parametrize("hq,hkv,q_len,kv_len", [(64, 32, [1, 3821], [182, 26060]),
+                                                 (64, 8, [1, 1, 3362], [3580, 1621, 3362]),
+                                                 (16, 8, [1] * 32 + [256], [1280] * 32 + [4096])])
+@pytest.mark.parametrize("resident", [0, 4096, 16384])
+def test_meta_mixed_plans_fit_the_static_workspace(hq, hkv, q_len, kv_len, resident):
+    """More wavefronts to fill make more splits, but never more partial results
+    than the library's fixed workspace holds."""
+    pages = [wl.pages_for(k) for k in kv_len]
+    bt = wl.block_tables(1, pages, sum(pages))
+    meta = D.dlfp_build_varlen_meta(D.make_dims(hq, hkv), q_len, kv_len, bt, sum(pages),
+                                    D.dlfp_tuning(0, 0, resident))
+    assert meta.workspace_bytes <= D.STATIC_WORKSPACE_BYTES
+
+
 def test_meta_errors():
     dims = D.make_dims(16, 8)
     bt = np.array([[0, 1, 2]], dtype=np.int32)
