@@ -2216,8 +2216,6 @@ int compute_units() {
   return cached[dev];
 }
 
-constexpr int FUSED_APPEND_MAX_WGS = 16;
-
 template <int G, bool APP>
 hipError_t launch(const Args& a, int grid, hipStream_t stream) {
   // Without prefill units: eight wavefronts to a unit while the units are few
@@ -2298,22 +2296,14 @@ int launch_mixed(const dlfp_dims* dims, const dlfp_meta* meta, const int32_t* d_
   a.v_new = static_cast<const uint16_t*>(v_new);
   a.num_append = app ? meta->num_append : 0;
   a.num_waiting = app ? meta->num_waiting_units : 0;
-  // Append workgroups in the launch: about two records per wavefront, a
-  // multiple of 8.  Past FUSED_APPEND_MAX_WGS of them the records get a launch
-  // of their own first: at the start of the attention launch each append
-  // workgroup holds a CU slot, which pushes long prefill units to share CUs
-  // (measured on Qwen3-0.6B shapes: chunks of 512-2048 prompt tokens took
-  // 15-20% longer in one launch, while chunks of 64-256 gained 6-8% per
-  // iteration from dropping the second launch).
-  a.app_wgs = a.num_append > 0 ? (int)(((int64_t)a.num_append + 63) / 64 * 8) : 0;
-  if (a.app_wgs > FUSED_APPEND_MAX_WGS) {
+  a.app_wgs = dlfp::append_workgroups(a.num_append);
+  if (a.num_append > 0 && a.app_wgs == 0) {
     Args r = a;
     r.app_wgs = (a.num_append + 3) / 4;
     r.num_waiting = 0;
     (void)hipGetLastError();
     append_records_kernel<<<r.app_wgs, THREADS, 0, stream>>>(r);
     if (hipGetLastError() != hipSuccess) return DLFP_EHIP;
-    a.app_wgs = 0;
     a.num_append = 0;
     a.num_waiting = 0;
   }

@@ -280,11 +280,11 @@ int dlfp_build_varlen_meta(const dlfp_dims* dims, const dlfp_tuning* tuning, int
   // Append workgroups of a one-launch iteration (none when the records take a
   // launch of their own), and the time of the decode share as wavefront units,
   // in microseconds: its bytes, and the queue's start, last units and merges.
-  int64_t app_wgs = 0;
-  for (int s = 0; s < num_seqs; ++s)
-    if (q_len[s] != 1) app_wgs += hkv * (q_len[s] / DLFP_PAGE_SIZE + 2);
-  app_wgs = ceil_div(app_wgs, 64) * 8;
-  if (app_wgs > 16) app_wgs = 0;
+  int64_t append_records = 0;
+  for (int s : prompts)
+    append_records +=
+        hkv * (ceil_div(kv_len[s], DLFP_PAGE_SIZE) - (kv_len[s] - q_len[s]) / DLFP_PAGE_SIZE);
+  const int64_t app_wgs = dlfp::append_workgroups(append_records);
   const double wave_est = dec_keys > 0 ? (double)dec_keys * (512 / 6.4e6) + 8.0 : 0.0;
   // Prefill units of a tile size and split: their number, the longest one's
   // keys, the most parts of a range.
@@ -680,14 +680,8 @@ int dlfp_build_varlen_meta(const dlfp_dims* dims, const dlfp_tuning* tuning, int
   // token).  A prefill unit waits for them when its last key lies in a page
   // from the one holding its sequence's first new token on.
   std::vector<Unit> appends;
-  {
-    int64_t n = 0;
-    for (int s = 0; s < num_seqs; ++s)
-      if (q_len[s] != 1) n += hkv * (q_len[s] / DLFP_PAGE_SIZE + 2);
-    appends.reserve((size_t)n);
-  }
-  for (int s = 0; s < num_seqs; ++s) {
-    if (q_len[s] == 1) continue;
+  appends.reserve((size_t)append_records);
+  for (int s : prompts) {
     const int64_t pos0 = kv_len[s] - q_len[s];
     for (int kh = 0; kh < hkv; ++kh)
       for (int64_t p = pos0; p < kv_len[s];) {

@@ -198,6 +198,30 @@ def test_meta_mixed_plans_fit_the_static_workspace(hq, hkv, q_len, kv_len, resid
     assert meta.workspace_bytes <= D.STATIC_WORKSPACE_BYTES
 
 
+def _append_workgroups(records):
+    """Workgroups of the one-launch form that write the append records; none above 128 records."""
+    wgs = -(-records // 64) * 8
+    return wgs if wgs <= 16 else 0
+
+
+@pytest.mark.parametrize("g", [1, 2, 4, 8])
+def test_meta_counts_the_append_workgroups_of_the_launch(g):
+    """A page-aligned chunk of 256 tokens and 8 KV heads make 128 append records, 16
+    workgroups of the launch: a plan of workgroup decode units leaves them their
+    slots (512 workgroups are resident), so none ends between 496 and 512 units."""
+    chunk, ctx = 256, 500
+    dims = D.make_dims(8 * g, 8)
+    for prefix in (0, 256):
+        for decoders in range(20, 63):
+            kv = [chunk + prefix] + [ctx] * decoders
+            pages = [wl.pages_for(k) for k in kv]
+            bt = np.zeros((len(kv), max(pages)), dtype=np.int32)
+            m = D.dlfp_build_varlen_meta(dims, [chunk] + [1] * decoders, kv, bt, 1)
+            assert m.num_append == 128
+            fits = m.num_units + _append_workgroups(m.num_append) <= 512
+            assert fits or m.num_units > 512, (g, prefix, decoders, m.num_units)
+
+
 def test_meta_errors():
     dims = D.make_dims(16, 8)
     bt = np.array([[0, 1, 2]], dtype=np.int32)
