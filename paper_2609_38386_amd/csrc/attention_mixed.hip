@@ -2307,23 +2307,14 @@ int launch_mixed(const dlfp_dims* dims, const dlfp_meta* meta, const int32_t* d_
     a.num_append = 0;
     a.num_waiting = 0;
   }
-  // Decode units beside prefill units.  When all workgroups fit the resident
-  // slots of the device (two per CU) even with a workgroup to each unit, each
-  // gets one: the launch is short and its end, where a wavefront's unit streams
-  // alone at a quarter of what the compute unit could take, is most of it
-  // (g = 8, 6 decoders of 250-2000 keys beside 47 new tokens: 18.9 -> 11.8 us;
-  // g = 4, 10 of 442-3536 beside 2: 21.7 -> 17.8 us).  Not for units of up to
-  // 128 keys, one step of a workgroup, which the built-in split makes where the
-  // prefill share sets the launch time (11 decoders of 38-304 keys beside 796
-  // tokens over 858, g = 2: 34.8 us, a workgroup each 35.3 us).  Otherwise
-  // enough workgroups to fill the slots, fewer when there are fewer units;
-  // they drain the decode queue.  Only those that find a slot left by the
-  // append and prefill workgroups from the start (at least 64) get units by
-  // position.
+  // Wavefronts' decode units beside prefill units: enough workgroups to fill the
+  // slots, fewer when there are fewer units; they drain the decode queue.  Only
+  // those that find a slot left by the append and prefill workgroups from the
+  // start (at least 64) get units by position.
   const int cus = compute_units();
   const int decode_units = meta->num_units - meta->num_prefill_units;
   const int ahead = meta->num_prefill_units + a.app_wgs;
-  a.wide = ahead + decode_units <= 2 * cus && meta->decode_split_tokens > 128;
+  a.wide = dlfp::decode_by_workgroup(*meta, cus);
   const int decode_wgs = a.wide ? decode_units : std::min((decode_units + 3) / 4, 2 * cus);
   const int slots = ahead < 2 * cus ? std::max(2 * cus - ahead, 64) : 2 * cus;
   a.decode_waves = 4 * decode_wgs;

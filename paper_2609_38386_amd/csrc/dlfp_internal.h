@@ -22,6 +22,24 @@ inline int append_workgroups(int64_t records) {
   return wgs <= 16 ? (int)wgs : 0;
 }
 
+// Whether the decode units beside prefill units are each the work of a
+// workgroup, else of a wavefront.  When all workgroups fit the resident slots of
+// the device (two per compute unit) even with a workgroup to each unit, each
+// gets one: the launch is short and its end, where a wavefront's unit streams
+// alone at a quarter of what the compute unit could take, is most of it (g = 8,
+// 6 decoders of 250-2000 keys beside 47 new tokens: 18.9 -> 11.8 us; g = 4, 10
+// of 442-3536 beside 2: 21.7 -> 17.8 us).  Not for units of up to 128 keys, one
+// step of a workgroup, which the built-in split makes where the prefill share
+// sets the launch time (11 decoders of 38-304 keys beside 796 tokens over 858,
+// g = 2: 34.8 us, a workgroup each 35.3 us).  The two round their probabilities
+// against different reference maxima, so the rule takes only what the metadata
+// holds: the append records count also where another call writes them, and the
+// one- and two-launch forms give equal bits.
+inline bool decode_by_workgroup(const dlfp_meta& m, int64_t compute_units) {
+  return (int64_t)m.num_units + append_workgroups(m.num_append) <= 2 * compute_units &&
+         m.decode_split_tokens > 128;
+}
+
 }  // namespace dlfp
 
 #endif  // DLFP_INTERNAL_H

@@ -187,3 +187,28 @@ def test_long_prompt_appended_inside_the_launch(dev, specs):
     assert 0 < it.meta.num_append <= 128, it.meta.num_append
     got = _fused_vs_two_calls(dev, dims, seqs, _pool_for(seqs), 9, label=f"long {specs}")
     _oracle_check(got, seqs, f"fused long prompt {specs}")
+
+
+@pytest.mark.parametrize("g,decoders,ctx,chunk,split,by_workgroup", [
+    (2, 62, 500, 4, 512, True),     # 504 units and 8 append workgroups: every slot taken
+    (2, 63, 500, 4, 512, False),    # 512 and 8
+    (2, 47, 500, 256, 512, False),  # 504 and 16
+    (8, 62, 270, 4, 0, None),       # around the edge as the built-in split cuts them
+    (8, 63, 270, 4, 0, None),
+])
+def test_both_forms_take_the_same_decode_units(dev, g, decoders, ctx, chunk, split, by_workgroup):
+    """Around 512 workgroups, the append workgroups of the one-launch form among
+    them: decode units are a workgroup's or a wavefront's in both forms, so the
+    bits are equal (the two round against different reference maxima)."""
+    shape = wl.AttnShape(8 * g, 8)
+    seqs = _seqs(shape, [(1, ctx)] * decoders + [(chunk, chunk)], seed=140 + decoders + g)
+    dims, tuning = D.make_dims(8 * g, 8), D.dlfp_tuning(split, 0, 0)
+    m = rt.Batch(dims, [s.q_len for s in seqs], [s.kv_len for s in seqs],
+                 wl.block_tables(1, [wl.pages_for(s.kv_len) for s in seqs], _pool_for(seqs)),
+                 _pool_for(seqs), dev, tuning=tuning).meta
+    if by_workgroup is not None:
+        workgroups = m.num_units + -(-m.num_append // 64) * 8
+        assert abs(workgroups - 512) <= 8 and (workgroups <= 512) == by_workgroup
+    got = _fused_vs_two_calls(dev, dims, seqs, _pool_for(seqs), 13, tuning=tuning,
+                              label=f"edge g={g} {decoders} decoders, chunk {chunk}")
+    _oracle_check(got, seqs, f"edge g={g} {decoders} decoders, chunk {chunk}")
