@@ -133,10 +133,10 @@ typedef struct {
  * decode unit is the work of a workgroup, and the decode split is the one in
  * equal parts (of at least 192 keys) that minimises an estimate of the launch
  * time.  So it is beside a prefill share that leaves workgroup slots (two per
- * compute unit) for all of them, when the estimate is under 0.9 of that of
- * wavefront units; else a decode unit beside a prefill share is a wavefront's
- * (also when split into units of up to 128 keys), and the split
- * is either sqrt(256 W / F) keys for W decode keys over the F wavefronts of the
+ * compute unit) for all of them, when the estimate is under that of wavefront
+ * units (under 0.85 of it beside tiles of more than 32 rows); else a decode
+ * unit beside a prefill share is a wavefront's (also when split into units of
+ * up to 128 keys), and the split is either sqrt(256 W / F) keys for W decode keys over the F wavefronts of the
  * workgroup slots the prefill units leave (several queue rounds), or the
  * split that fits one round and best evens the decode workgroups over the
  * CUs, whichever an estimate of the launch time favours.  A range longer than

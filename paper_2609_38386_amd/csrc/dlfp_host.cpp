@@ -183,10 +183,12 @@ int dlfp_build_varlen_meta(const dlfp_dims* dims, const dlfp_tuning* tuning, int
     }
     return best_sp;
   };
-  // Decode split of a launch without prefill units: one unit per workgroup of
-  // eight wavefronts, one workgroup per compute unit.  Every candidate (the
-  // longest range in k equal parts, of at least 192 keys: eight wavefronts take
-  // 256 at a time; and the longest unit there is) is weighed by an estimate of the launch time in
+  std::vector<int> prompts, decoders;  // sequences of the prefill and of the decode share
+  for (int s = 0; s < num_seqs; ++s) (q_len[s] == 1 ? decoders : prompts).push_back(s);
+  // Split of decode units that are each the work of a workgroup, one workgroup
+  // per compute unit.  Every candidate (the longest range in k equal parts, of
+  // at least 192 keys: eight wavefronts take 256 at a time; and the longest unit
+  // there is) is weighed by an estimate of the decode share's time in
   // microseconds.  Up to one unit per compute unit they all stream side by
   // side: while n units still have keys, 64 more keys of each (32 KiB) take
   // n x 32 KiB at the device's 6.4 TB/s or 32 KiB at a compute unit's 60 GB/s,
@@ -198,13 +200,17 @@ int dlfp_build_varlen_meta(const dlfp_dims* dims, const dlfp_tuning* tuning, int
   // average, and the launches take 0.79x the time of the wavefront units and
   // splits used before (geometric mean; 8.6-10.7 -> 4.9-7 us for the smallest).
   // Beside `ahead` prefill and append workgroups (0: alone) the units have to
-  // fit into the slots those leave, two workgroups per compute unit, and past
-  // one unit per compute unit half of the longest unit runs alone at the end.
-  // Returns the split and the estimate (infinite: no split fits).
-  auto wide_split = [&](int64_t ahead, double* est) -> int64_t {
+  // fit into the slots those leave, two workgroups per compute unit; when they
+  // need a second workgroup on some compute unit, that one's unit takes twice as
+  // long; and past one unit per compute unit half of the longest unit runs alone
+  // at the end.  No split that fits: an infinite estimate.
+  struct WideSplit {
+    int64_t split, units;
+    double est;
+  };
+  auto wide_split = [&](int64_t ahead) {
     const int64_t cus = std::max<int64_t>(1, resident / 8);
-    int64_t best_sp = DLFP_MAX_DECODE_UNIT_KEYS;
-    double best = std::numeric_limits<double>::infinity();
+    WideSplit best = {DLFP_MAX_DECODE_UNIT_KEYS, 0, std::numeric_limits<double>::infinity()};
     const int64_t least_parts = ceil_div(std::max<int32_t>(max_kv, 1), DLFP_MAX_DECODE_UNIT_KEYS);
     for (int64_t k = 0;; k = k ? k + std::max<int64_t>(1, k / 4) : least_parts) {
       const int64_t parts = k ? round_up(ceil_div(max_kv, k), 32) : DLFP_MAX_DECODE_UNIT_KEYS;
@@ -213,7 +219,7 @@ int dlfp_build_varlen_meta(const dlfp_dims* dims, const dlfp_tuning* tuning, int
       int64_t units = 0, ending[BUCKETS + 1] = {0};
       int64_t longest = 0;
       bool split = false;
-      for (int s = 0; s < num_seqs; ++s) {
+      for (int s : decoders) {
         const int64_t kl = kv_len[s], n0 = ceil_div(kl, sp);
         int64_t n = n0, part = kl;
         if (n0 > 1) {
@@ -226,11 +232,12 @@ int dlfp_build_varlen_meta(const dlfp_dims* dims, const dlfp_tuning* tuning, int
         ending[ceil_div(part, STEP)] += n * hkv;
       }
       if (ahead > 0 && units > 2 * cus - ahead) break;  // a shorter split has more
+      const double share = ahead > 0 && ahead + units > cus ? 2.0 : 1.0;
       double e = split ? 2.5 : 0.0;
       if (units <= cus) {
         int64_t n = units;
         for (int b = 1; b <= BUCKETS && n > 0; ++b) {
-          e += std::max((double)n * (STEP * 512 / 6.4e6), STEP * 512 / 60e3);
+          e += std::max((double)n * (STEP * 512 / 6.4e6), share * (STEP * 512 / 60e3));
           n -= ending[b];
         }
       } else if (ahead > 0) {
@@ -238,19 +245,12 @@ int dlfp_build_varlen_meta(const dlfp_dims* dims, const dlfp_tuning* tuning, int
       } else {
         e += (double)dec_keys * (512 / 6.4e6) + 3.0 * (double)units / (double)cus;
       }
-      if (e < best) {
-        best = e;
-        best_sp = sp;
-      }
+      if (e < best.est) best = {sp, units, e};
       if (sp <= 192) break;
     }
-    *est = best;
-    return best_sp;
+    return best;
   };
   // Prefill units of the iteration for a tile size and key split.
-  std::vector<int> prompts;  // sequences of the prefill share
-  for (int s = 0; s < num_seqs; ++s)
-    if (q_len[s] != 1) prompts.push_back(s);
   auto prefill_units = [&](int64_t tt, int64_t split) {
     int64_t n = 0;
     for (int s : prompts) {
@@ -318,10 +318,11 @@ int dlfp_build_varlen_meta(const dlfp_dims* dims, const dlfp_tuning* tuning, int
   // estimates favour, all workgroups within the two a CU holds.  The decode
   // share counts as small when its wavefront units, four to a workgroup at the
   // split they would take without prefill, leave that room too, or when units
-  // of a workgroup fit beside the tiles and are much faster.  (Shapes of 1-160
-  // decoders of 16-30000 keys and 2-3000 new tokens over up to 12000, g = 1-8:
-  // 0.82x the launch time of the policy and code before, geometric mean of 120,
-  // none slower by more than 1.5%; prefill alone 0.75x over 36.)
+  // of a workgroup fit beside the tiles and are much faster, and the tiles do
+  // not then last far beyond the decode share (54 decoders of 53-396 keys beside
+  // 8 prompts of 2 tokens, one over 6376, g = 4: 63.9 us with its tiles whole,
+  // 32.5 at 1024 keys beside wavefront units).  (Prefill alone 0.75x the launch
+  // time of the policy and code before, 36 shapes.)
   if (!split_p && !tn.prefill_tile_tokens && pre_keys > 0) {
     const int64_t cus = resident / 8, slots = resident / 4;
     const int small = std::max(1, 32 / g);
@@ -332,17 +333,17 @@ int dlfp_build_varlen_meta(const dlfp_dims* dims, const dlfp_tuning* tuning, int
       double best = std::numeric_limits<double>::infinity();
       for (int64_t sp : {DLFP_MAX_PREFILL_UNIT_KEYS, 4096, 2048, 1024, 512, 256}) {
         int64_t n = 0;
-        double wide = 0;
         double e = prefill_est(small, sp, true, dec_wgs, &n);
         if (n + dec_wgs > slots) break;
         if (dec_keys > 0) {
-          wide_split(n + app_wgs, &wide);
-          if (wide < (wave_fits ? 0.9 : 0.75) * wave_est)
-            e = std::max(e, wide);
+          const WideSplit wide = wide_split(n + app_wgs);
+          if (wide.est < (wave_fits ? 1.0 : 0.75) * wave_est)
+            e = std::max(prefill_est(small, sp, true, wide.units, &n), wide.est);
           else if (wave_fits)
             e = std::max(prefill_est(small, sp, false, dec_wgs, &n), wave_est);
           else
             continue;
+          if (!wave_fits && e > 1.5 * wave_est) continue;
         }
         if (e < best) {
           best = e;
@@ -481,26 +482,28 @@ int dlfp_build_varlen_meta(const dlfp_dims* dims, const dlfp_tuning* tuning, int
     }
   }
   // Decode units of a workgroup beside the prefill units where their estimate
-  // is clearly the lower one and, beside tall tiles, the decode share is not
-  // hidden behind them anyway: more workgroups then only crowd the tiles (11
-  // decoders of 38-304 keys beside 796 tokens over 858, g = 2: 34.6 against
-  // 35.4 us; 6 of 796-6368 beside 321 over 1359: 40.1 against 33.3 us; 30 of
-  // 906-7248 beside 20 tokens, g = 4, where they do not fit well: 85.2 against
-  // 93.8 us).
+  // is the lower one (beside 713 plans of short tiles they take 0.78x the time
+  // of wavefront units where it is up to 0.85x theirs, 0.87x up to 0.9, 0.97x up
+  // to 1, 1.01x up to 1.1, 1.08x up to 1.2) and, beside tall tiles, clearly so
+  // (0.93x up to 0.85, even from there) with the decode share not hidden behind
+  // them anyway: more workgroups then only crowd the tiles (11 decoders of
+  // 38-304 keys beside 796 tokens over 858, g = 2: 34.6 against 35.4 us; 6 of
+  // 796-6368 beside 321 over 1359: 40.1 against 33.3 us; 32 of 536-2024 beside
+  // 512 over 2048: 51.6 against 48.5 us).
   const bool tall = tile_tokens * g > 32;
   int64_t pre_units = 0;
   const double pre_est = prefill_est(tile_tokens, split_p, !tall, 0, &pre_units);
   int64_t split_d = tn.decode_split_tokens;
   if (!split_d) {
-    double wide = 0;
-    const int64_t sd = wide_split(pre_units > 0 ? pre_units + app_wgs : 0, &wide);
+    const WideSplit wide = wide_split(pre_units > 0 ? pre_units + app_wgs : 0);
     const bool use_wide =
-        pre_units == 0 || (wide < 0.9 * wave_est && (!tall || wave_est > 0.5 * pre_est));
+        pre_units == 0 || (tall ? wide.est < 0.85 * wave_est && wave_est > 0.5 * pre_est
+                                : wide.est < wave_est);
     // As wavefront units the decode share starts in the workgroup slots (two
     // per CU, four wavefronts each) that the prefill units leave, at least 64;
     // when the prefill units take them all, it runs as they retire.
     split_d = use_wide
-                  ? sd
+                  ? wide.split
                   : decode_split(pre_units < resident / 4
                                      ? std::max<int64_t>(resident / 4 - pre_units, 64)
                                      : resident / 4);

@@ -222,6 +222,24 @@ def test_meta_counts_the_append_workgroups_of_the_launch(g):
             assert fits or m.num_units > 512, (g, prefix, decoders, m.num_units)
 
 
+@pytest.mark.parametrize("g,decoders", [(2, [64, 100, 160, 256]), (1, list(range(512, 2048, 48))),
+                                        (4, [2000, 9000]), (8, [300] * 8)])
+def test_meta_decode_plan_is_the_decoders_own(g, decoders):
+    """The decode share's plan depends on the decoders and on the slots that the
+    prompt leaves, not on the prompt's keys: whole tiles of 32 rows are as many
+    over any cached prefix, and the decode units beside them stay the same."""
+    q = 64
+    plans = []
+    for prefix in (0, 512, 4096, 16384):
+        kv = [q + prefix] + decoders
+        bt = np.zeros((len(kv), max(wl.pages_for(k) for k in kv)), dtype=np.int32)
+        m = D.dlfp_build_varlen_meta(D.make_dims(8 * g, 8), [q] + [1] * len(decoders), kv, bt, 1,
+                                     D.dlfp_tuning(0, 32768, 0, 32 // g))
+        plans.append((m.num_prefill_units, m.decode_split_tokens,
+                      m.work[m.num_prefill_units:].tobytes()))
+    assert all(p == plans[0] for p in plans), [p[:2] for p in plans]
+
+
 def test_meta_errors():
     dims = D.make_dims(16, 8)
     bt = np.array([[0, 1, 2]], dtype=np.int32)
