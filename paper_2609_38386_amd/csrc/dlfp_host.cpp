@@ -414,9 +414,17 @@ int dlfp_build_varlen_meta(const dlfp_dims* dims, const dlfp_tuning* tuning, int
     // and its bytes at the rate the slots left to it draw (all of it from 400
     // up), at the full rate once the prefill units are done.  (48 shapes of
     // 12-160 decoders beside 33-1500 tokens over up to 12000 keys: 0.965x on
-    // average, none slower; the estimate is good to 9%, so a smaller lead is
-    // left alone.)
-    auto launch_est = [&](int64_t tt, int64_t sp, int64_t* units) {
+    // average; the estimate is good to 9%, so a smaller lead is left alone.)
+    // Past one and a half units per compute unit few slots are left, which a
+    // decode share that fits them in one round would get as units of thousands
+    // of keys, one wavefront each: where it is not clearly the shorter share
+    // such splits are left out (8 decoders of 2741-14421 keys beside 8 prompts
+    // of 100-400 tokens, g = 2: 440 units 138.1 us, 344 of them 90.5; a decode
+    // share of many rounds gains from them: 148 decoders beside 4 prompts, 496
+    // units 87.9 us, 328 of them 120.3).
+    int64_t least_units = 0;  // decode units at the longest split
+    for (int s : decoders) least_units += hkv * ceil_div(kv_len[s], DLFP_MAX_DECODE_UNIT_KEYS);
+    auto launch_est = [&](int64_t tt, int64_t sp, int64_t* units, double* prefill = nullptr) {
       int64_t n = 0, longest = 0, parts = 1;
       shape(tt, sp, &n, &longest, &parts);
       *units = n;
@@ -425,6 +433,7 @@ int dlfp_build_varlen_meta(const dlfp_dims* dims, const dlfp_tuning* tuning, int
       const double pre = 10.0 + per_key * (double)longest * (1.0 + 0.72 * crowd) *
                                     std::max(1.0, (double)n / (2.0 * (double)target)) +
                          (parts > 1 ? 2.4 + 0.5 * (double)parts : 0.0);
+      if (prefill) *prefill = pre;
       const double rate = std::min(1.0, (double)std::max<int64_t>(2 * target - n, 64) / 400.0);
       const double work = 14.0 + (double)dec_keys * (512 / 6.4e6);
       const double dec = work <= rate * pre ? work / rate : pre + work - rate * pre;
@@ -444,8 +453,12 @@ int dlfp_build_varlen_meta(const dlfp_dims* dims, const dlfp_tuning* tuning, int
         const int64_t sp = round_up(ceil_div(max_kend, k), KV_GRANULE_PREFILL);
         if (sp > DLFP_MAX_PREFILL_UNIT_KEYS) continue;
         if (k > 1 && sp < 256) break;
-        const double e = launch_est(tt, sp, &n);
+        double pre = 0;
+        const double e = launch_est(tt, sp, &n, &pre);
         if (n > 2 * target) break;
+        if (2 * n > 3 * target && wave_est > 0.5 * pre &&
+            least_units <= 4 * std::max<int64_t>(2 * target - n, 64))
+          continue;
         if (e < best) {
           best = e;
           tile_tokens = (int)tt;

@@ -240,6 +240,21 @@ def test_meta_decode_plan_is_the_decoders_own(g, decoders):
     assert all(p == plans[0] for p in plans), [p[:2] for p in plans]
 
 
+@pytest.mark.parametrize("decoders,lo,hi", [(4, 10240, 38400), (8, 2816, 14336), (16, 1024, 6400),
+                                            (28, 608, 4256)])
+def test_meta_prefill_splits_leave_the_decode_share_its_slots(decoders, lo, hi):
+    """A decode share that one round of wavefronts could hold is not crowded into
+    the last few slots (units of 2500-3900 keys, one wavefront each) by prefill
+    splits past one and a half units per compute unit."""
+    prompts = [(900, 550), (560, 6800), (1100, 980)]
+    kv = [q + p for q, p in prompts] + [lo + (hi - lo) * i // (decoders - 1)
+                                        for i in range(decoders)]
+    bt = np.zeros((len(kv), max(wl.pages_for(k) for k in kv)), dtype=np.int32)
+    m = D.dlfp_build_varlen_meta(D.make_dims(16, 8), [q for q, _ in prompts] + [1] * decoders, kv,
+                                 bt, 1)
+    assert m.decode_split_tokens <= 2048, (m.num_prefill_units, m.decode_split_tokens)
+
+
 def test_meta_errors():
     dims = D.make_dims(16, 8)
     bt = np.array([[0, 1, 2]], dtype=np.int32)
