@@ -17,6 +17,10 @@ namespace {
 
 int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 int64_t round_up(int64_t a, int64_t b) { return ceil_div(a, b) * b; }
+// The same for counts of keys below 2^31 and divisors up to 2^31: the split
+// policy divides once per sequence or tile and candidate, and a 32-bit division
+// takes half the time.
+uint32_t ceil_div32(uint32_t a, uint32_t b) { return (a + b - 1) / b; }
 // Prefill key ranges start on a 64-key tile.
 constexpr int64_t KV_GRANULE_PREFILL = 64;
 
@@ -141,25 +145,28 @@ int dlfp_build_varlen_meta(const dlfp_dims* dims, const dlfp_tuning* tuning, int
   // against the sqrt split by these estimates; ties go to the longer split.
   int32_t max_kv = 0;
   int64_t dec_keys = 0;
-  for (int s = 0; s < num_seqs; ++s)
-    if (q_len[s] == 1) {
-      max_kv = std::max(max_kv, kv_len[s]);
-      dec_keys += (int64_t)kv_len[s] * hkv;
-    }
+  std::vector<int> prompts, decoders;  // sequences of the prefill and of the decode share
+  prompts.reserve(num_seqs);
+  decoders.reserve(num_seqs);
+  for (int s = 0; s < num_seqs; ++s) (q_len[s] == 1 ? decoders : prompts).push_back(s);
+  for (int s : decoders) {
+    max_kv = std::max(max_kv, kv_len[s]);
+    dec_keys += (int64_t)kv_len[s] * hkv;
+  }
   auto decode_split = [&](int64_t slots) -> int64_t {
     slots = std::max<int64_t>(1, slots);
     const int64_t free_waves = 4 * slots;
     const int64_t cu_cap = std::max<int64_t>(1, std::min<int64_t>(resident / 8, slots));
     auto units_and_longest = [&](int64_t sp, int64_t* longest) {
       int64_t n_units = 0;
-      *longest = 0;
-      for (int s = 0; s < num_seqs; ++s) {
-        if (q_len[s] != 1) continue;
-        const int64_t n = ceil_div(kv_len[s], sp);
-        n_units += hkv * n;
-        *longest = std::max(*longest, round_up(ceil_div(kv_len[s], n), DLFP_PAGE_SIZE));
+      uint32_t part = 0;
+      for (int s : decoders) {
+        const uint32_t n = ceil_div32(kv_len[s], (uint32_t)sp);
+        n_units += n;
+        part = std::max(part, ceil_div32(kv_len[s], n));
       }
-      return n_units;
+      *longest = round_up(part, DLFP_PAGE_SIZE);
+      return n_units * hkv;
     };
     const double root = std::sqrt(256.0 * (double)dec_keys / (double)free_waves);
     const int64_t s0 = std::clamp<int64_t>(round_up((int64_t)std::ceil(root), DLFP_PAGE_SIZE), 128,
@@ -173,6 +180,7 @@ int dlfp_build_varlen_meta(const dlfp_dims* dims, const dlfp_tuning* tuning, int
     const int64_t top = std::min<int64_t>(round_up(std::max<int32_t>(max_kv, 128), DLFP_PAGE_SIZE),
                                           DLFP_MAX_DECODE_UNIT_KEYS);
     for (int64_t sp = 128; sp <= top; sp = round_up(sp + std::max<int64_t>(16, sp / 16), 16)) {
+      if (dec_keys > free_waves * sp) continue;  // too many units whatever their lengths
       const int64_t n_units = units_and_longest(sp, &longest);
       if (n_units > free_waves) continue;
       const double e = (double)ceil_div(ceil_div(n_units, 4), cu_cap) * (double)(longest + 256);
@@ -183,8 +191,6 @@ int dlfp_build_varlen_meta(const dlfp_dims* dims, const dlfp_tuning* tuning, int
     }
     return best_sp;
   };
-  std::vector<int> prompts, decoders;  // sequences of the prefill and of the decode share
-  for (int s = 0; s < num_seqs; ++s) (q_len[s] == 1 ? decoders : prompts).push_back(s);
   // Split of decode units that are each the work of a workgroup, one workgroup
   // per compute unit.  Every candidate (the longest range in k equal parts, of
   // at least 192 keys: eight wavefronts take 256 at a time; and the longest unit
@@ -208,45 +214,63 @@ int dlfp_build_varlen_meta(const dlfp_dims* dims, const dlfp_tuning* tuning, int
     int64_t split, units;
     double est;
   };
-  auto wide_split = [&](int64_t ahead) {
+  // What a candidate makes of the decoders, whatever stands beside them: its
+  // units, the longest one's keys, and the time with all of them side by side,
+  // on compute units of their own or shared ones.
+  struct WideCandidate {
+    int64_t split, units, longest;
+    double own, shared;  // (or the time of its merge, with more units than that)
+  };
+  std::vector<WideCandidate> wide_candidates;
+  auto add_wide_candidates = [&]() {
     const int64_t cus = std::max<int64_t>(1, resident / 8);
-    WideSplit best = {DLFP_MAX_DECODE_UNIT_KEYS, 0, std::numeric_limits<double>::infinity()};
     const int64_t least_parts = ceil_div(std::max<int32_t>(max_kv, 1), DLFP_MAX_DECODE_UNIT_KEYS);
     for (int64_t k = 0;; k = k ? k + std::max<int64_t>(1, k / 4) : least_parts) {
-      const int64_t parts = k ? round_up(ceil_div(max_kv, k), 32) : DLFP_MAX_DECODE_UNIT_KEYS;
-      const int64_t sp = std::clamp<int64_t>(parts, 192, DLFP_MAX_DECODE_UNIT_KEYS);
+      const int64_t equal = k ? round_up(ceil_div(max_kv, k), 32) : DLFP_MAX_DECODE_UNIT_KEYS;
+      const uint32_t sp = (uint32_t)std::clamp<int64_t>(equal, 192, DLFP_MAX_DECODE_UNIT_KEYS);
       constexpr int STEP = 64, BUCKETS = DLFP_MAX_DECODE_UNIT_KEYS / STEP;
       int64_t units = 0, ending[BUCKETS + 1] = {0};
-      int64_t longest = 0;
+      uint32_t longest = 0;
       bool split = false;
       for (int s : decoders) {
-        const int64_t kl = kv_len[s], n0 = ceil_div(kl, sp);
-        int64_t n = n0, part = kl;
+        const uint32_t kl = kv_len[s], n0 = ceil_div32(kl, sp);
+        uint32_t n = n0, part = kl;
         if (n0 > 1) {
-          part = round_up(ceil_div(kl, n0), DLFP_PAGE_SIZE);
-          n = ceil_div(kl, part);
+          part = (ceil_div32(kl, n0) + DLFP_PAGE_SIZE - 1) / DLFP_PAGE_SIZE * DLFP_PAGE_SIZE;
+          n = ceil_div32(kl, part);
           split = true;
         }
-        units += n * hkv;
+        units += n;
         longest = std::max(longest, part);
-        ending[ceil_div(part, STEP)] += n * hkv;
+        ending[(part + STEP - 1) / STEP] += n;
       }
-      if (ahead > 0 && units > 2 * cus - ahead) break;  // a shorter split has more
-      const double share = ahead > 0 && ahead + units > cus ? 2.0 : 1.0;
-      double e = split ? 2.5 : 0.0;
-      if (units <= cus) {
-        int64_t n = units;
+      const double merge = split ? 2.5 : 0.0;
+      WideCandidate c = {sp, units * hkv, longest, merge, merge};
+      if (c.units <= cus) {
+        int64_t n = c.units;
         for (int b = 1; b <= BUCKETS && n > 0; ++b) {
-          e += std::max((double)n * (STEP * 512 / 6.4e6), share * (STEP * 512 / 60e3));
-          n -= ending[b];
+          const double bytes = (double)n * (STEP * 512 / 6.4e6);
+          c.own += std::max(bytes, STEP * 512 / 60e3);
+          c.shared += std::max(bytes, 2.0 * (STEP * 512 / 60e3));
+          n -= ending[b] * hkv;
         }
-      } else if (ahead > 0) {
-        e += (double)dec_keys * (512 / 6.4e6) + 0.5 * longest * (512 / 60e3);
-      } else {
-        e += (double)dec_keys * (512 / 6.4e6) + 3.0 * (double)units / (double)cus;
       }
-      if (e < best.est) best = {sp, units, e};
+      wide_candidates.push_back(c);
       if (sp <= 192) break;
+    }
+  };
+  auto wide_split = [&](int64_t ahead) {
+    const int64_t cus = std::max<int64_t>(1, resident / 8);
+    if (wide_candidates.empty()) add_wide_candidates();
+    WideSplit best = {DLFP_MAX_DECODE_UNIT_KEYS, 0, std::numeric_limits<double>::infinity()};
+    for (const WideCandidate& c : wide_candidates) {
+      if (ahead > 0 && c.units > 2 * cus - ahead) break;  // a shorter split has more
+      double e = ahead > 0 && ahead + c.units > cus ? c.shared : c.own;
+      if (c.units > cus && ahead > 0)
+        e += (double)dec_keys * (512 / 6.4e6) + 0.5 * (double)c.longest * (512 / 60e3);
+      else if (c.units > cus)
+        e += (double)dec_keys * (512 / 6.4e6) + 3.0 * (double)c.units / (double)cus;
+      if (e < best.est) best = {c.split, c.units, e};
     }
     return best;
   };
@@ -254,9 +278,11 @@ int dlfp_build_varlen_meta(const dlfp_dims* dims, const dlfp_tuning* tuning, int
   auto prefill_units = [&](int64_t tt, int64_t split) {
     int64_t n = 0;
     for (int s : prompts) {
-      const int64_t pos0 = kv_len[s] - q_len[s];
-      for (int64_t t0 = 0; t0 < q_len[s]; t0 += tt)
-        n += hkv * ceil_div(pos0 + t0 + std::min<int64_t>(tt, q_len[s] - t0), split);
+      // Keys of the tiles: pos0 + tt, pos0 + 2 tt, ..., the last one's all.
+      const uint32_t all = kv_len[s], sp = (uint32_t)split;
+      int64_t parts = ceil_div32(all, sp);
+      for (int64_t k = (int64_t)all - q_len[s] + tt; k < all; k += tt) parts += ceil_div32((uint32_t)k, sp);
+      n += hkv * parts;
     }
     return n;
   };
@@ -289,16 +315,27 @@ int dlfp_build_varlen_meta(const dlfp_dims* dims, const dlfp_tuning* tuning, int
   // Prefill units of a tile size and split: their number, the longest one's
   // keys, the most parts of a range.
   auto shape = [&](int64_t tt, int64_t sp, int64_t* units, int64_t* longest, int64_t* parts) {
-    for (int s : prompts) {
-      const int64_t pos0 = kv_len[s] - q_len[s];
-      for (int64_t t0 = 0; t0 < q_len[s]; t0 += tt) {
-        const int64_t kend = pos0 + t0 + std::min<int64_t>(tt, q_len[s] - t0);
-        const int64_t part = round_up(ceil_div(kend, ceil_div(kend, sp)), KV_GRANULE_PREFILL);
-        *units += hkv * ceil_div(kend, part);
-        *longest = std::max(*longest, std::min(part, kend));
-        *parts = std::max(*parts, ceil_div(kend, part));
+    int64_t n = 0;
+    uint32_t longest_part = 0, most = 0;
+    auto tile = [&](uint32_t keys) {
+      uint32_t cut = 1, part = keys;
+      if (keys > (uint32_t)sp) {
+        part = ceil_div32(keys, ceil_div32(keys, (uint32_t)sp));
+        part = (part + KV_GRANULE_PREFILL - 1) / KV_GRANULE_PREFILL * KV_GRANULE_PREFILL;
+        cut = ceil_div32(keys, part);
       }
+      n += cut;
+      longest_part = std::max(longest_part, std::min(part, keys));
+      most = std::max(most, cut);
+    };
+    for (int s : prompts) {
+      const int64_t all = kv_len[s];
+      for (int64_t k = all - q_len[s] + tt; k < all; k += tt) tile((uint32_t)k);
+      tile((uint32_t)all);
     }
+    *units += n * hkv;
+    *longest = std::max<int64_t>(*longest, longest_part);
+    *parts = std::max<int64_t>(*parts, most);
   };
   // Time of the prefill share in microseconds: a fixed part, the merge of its
   // splits, and its longest unit, with the compute units' workgroups (`others`
@@ -447,7 +484,10 @@ int dlfp_build_varlen_meta(const dlfp_dims* dims, const dlfp_tuning* tuning, int
       if (q_len[s] != 1) max_kend = std::max<int64_t>(max_kend, kv_len[s]);
     constexpr double AHEAD = 0.8 * 0.8 * 0.8;  // 20% ahead, in the estimate's sixth power
     double best = roomy ? AHEAD * AHEAD * launch_est(tile_tokens, split_p, &n) : 0.0;
+    const double work = 14.0 + (double)dec_keys * (512 / 6.4e6);
+    const double least = work * work * work * work * work * work;  // of any estimate
     for (int rows : {DLFP_TILE_ROWS, DLFP_TILE_ROWS / 2, DLFP_TILE_ROWS / 4}) {
+      if (least >= best) break;
       const int64_t tt = std::max(1, rows / g);
       for (int64_t k : {1, 2, 3, 4, 5, 6, 8, 12}) {
         const int64_t sp = round_up(ceil_div(max_kend, k), KV_GRANULE_PREFILL);
@@ -548,11 +588,11 @@ int dlfp_build_varlen_meta(const dlfp_dims* dims, const dlfp_tuning* tuning, int
   // (decode units that run in several queue rounds: the queue hands out the
   // longest units first, so these short pieces even out the end of the launch).
   std::vector<int64_t> cut;
-  auto emit = [&](int s, int kh, int64_t t0, int64_t nt, int64_t kend, int64_t split,
-                  int64_t granule, int kind, bool tail = false) {
-    int64_t nsp = ceil_div(kend, split);
-    const int64_t part = round_up(ceil_div(kend, nsp), granule);
-    nsp = ceil_div(kend, part);
+  auto cut_range = [&](int64_t kend, int64_t split, int64_t granule, bool tail = false) {
+    const uint32_t keys = (uint32_t)kend;
+    const uint32_t equal = ceil_div32(keys, ceil_div32(keys, (uint32_t)split));
+    const int64_t part = ((int64_t)equal + granule - 1) & -granule;  // a power of two
+    const int64_t nsp = equal == keys ? 1 : ceil_div32(keys, (uint32_t)part);
     cut.clear();
     for (int64_t j = 0; j < nsp; ++j) cut.push_back(j * part);
     if (tail) {
@@ -564,7 +604,10 @@ int dlfp_build_varlen_meta(const dlfp_dims* dims, const dlfp_tuning* tuning, int
       }
     }
     cut.push_back(kend);
-    nsp = (int64_t)cut.size() - 1;
+  };
+  // The units of the range cut last, for one KV head.
+  auto emit = [&](int s, int kh, int64_t t0, int64_t nt, int kind) {
+    const int64_t nsp = (int64_t)cut.size() - 1;
     const int32_t grp = nsp > 1 ? groups++ : -1;
     if (nsp > 1) group_rows.push_back(nt * g);
     for (int64_t j = 0; j < nsp; ++j) {
@@ -604,21 +647,20 @@ int dlfp_build_varlen_meta(const dlfp_dims* dims, const dlfp_tuning* tuning, int
     int64_t t0, nt, kend;
   };
   std::vector<Tile> tiles;
-  for (int kh = 0; kh < hkv; ++kh) {
-    tiles.clear();
-    for (int s = 0; s < num_seqs; ++s) {
-      if (q_len[s] == 1) continue;
-      const int64_t pos0 = kv_len[s] - q_len[s];
-      for (int64_t t0 = 0; t0 < q_len[s]; t0 += tile_tokens) {
-        const int64_t nt = std::min<int64_t>(tile_tokens, q_len[s] - t0);
-        tiles.push_back(Tile{s, t0, nt, pos0 + t0 + nt});
-      }
+  for (int s : prompts) {
+    const int64_t pos0 = kv_len[s] - q_len[s];
+    for (int64_t t0 = 0; t0 < q_len[s]; t0 += tile_tokens) {
+      const int64_t nt = std::min<int64_t>(tile_tokens, q_len[s] - t0);
+      tiles.push_back(Tile{s, t0, nt, pos0 + t0 + nt});
     }
-    std::stable_sort(tiles.begin(), tiles.end(),
-                     [](const Tile& x, const Tile& y) { return x.kend > y.kend; });
-    for (const Tile& t : tiles)
-      emit(t.s, kh, t.t0, t.nt, t.kend, split_p, KV_GRANULE_PREFILL, DLFP_KIND_PREFILL);
   }
+  std::stable_sort(tiles.begin(), tiles.end(),
+                   [](const Tile& x, const Tile& y) { return x.kend > y.kend; });
+  for (int kh = 0; kh < hkv; ++kh)
+    for (const Tile& t : tiles) {
+      cut_range(t.kend, split_p, KV_GRANULE_PREFILL);
+      emit(t.s, kh, t.t0, t.nt, DLFP_KIND_PREFILL);
+    }
   const int64_t num_prefill = (int64_t)units.size();
   // Decode units that run in a few rounds (more units than the device takes at
   // once, but not so many that the last round is a small part of the launch
@@ -638,10 +680,9 @@ int dlfp_build_varlen_meta(const dlfp_dims* dims, const dlfp_tuning* tuning, int
     decode_tail = num_prefill > 0 ? n_dec > 4 * slots_d && n_dec <= 24 * slots_d
                                   : n_dec > cus_d && n_dec <= 8 * cus_d && dec_keys >= 2048 * n_dec;
   }
-  for (int s = 0; s < num_seqs; ++s) {
-    if (q_len[s] != 1) continue;
-    for (int kh = 0; kh < hkv; ++kh)
-      emit(s, kh, 0, 1, kv_len[s], split_d, DLFP_PAGE_SIZE, DLFP_KIND_DECODE, decode_tail);
+  for (int s : decoders) {
+    cut_range(kv_len[s], split_d, DLFP_PAGE_SIZE, decode_tail);
+    for (int kh = 0; kh < hkv; ++kh) emit(s, kh, 0, 1, DLFP_KIND_DECODE);
   }
   // Decode wavefronts take units in list order from a queue: longest first,
   // ties in emission order (a stable counting sort on the key count, which the
