@@ -130,9 +130,10 @@ typedef struct {
  * unit clearly ahead; a prefill share alone
  * takes 128-row tiles and the split (a multiple of 64 keys, at least 1024)
  * that minimises an estimate of the launch time.  Without a prefill share a
- * decode unit is the work of a workgroup, and the decode split is the one in
- * equal parts (of at least 192 keys) that minimises an estimate of the launch
- * time.  So it is beside a prefill share that leaves workgroup slots (two per
+ * decode unit is the work of a workgroup (513 to 2048 units of at most 192 keys:
+ * of a wavefront), and the decode split is the one in equal parts (of at least
+ * 192 keys) that minimises an estimate of the launch time, the longest context
+ * when that cuts nothing.  So it is beside a prefill share that leaves workgroup slots (two per
  * compute unit) for all of them, when the estimate is under that of wavefront
  * units (under 0.85 of it beside tiles of more than 32 rows); else a decode
  * unit beside a prefill share is a wavefront's (also when split into units of

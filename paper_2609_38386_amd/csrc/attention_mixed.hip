@@ -4,9 +4,8 @@
 // the chunk) of Eq. 1, Sec. 2.1, served by one grid.
 //
 // Grid: the work list's prefill units first, one 256-thread workgroup each,
-// then decode units: four per workgroup (one per wavefront), or one when the
-// launch has no prefill units or is so small that all its workgroups are
-// resident at once.
+// then decode units: four per workgroup (one per wavefront), or one
+// (dlfp::decode_by_workgroup says when).
 //
 // Prefill unit = (sequence, KV head, tile of 128 query rows, key split).
 // Rows are the tile's tokens x the g query heads sharing the KV head, so each
@@ -114,7 +113,7 @@ struct Args {
   int32_t lead;          // prefill workgroups before the first decode workgroup
   int32_t decode_lead;   // decode workgroups before the remaining prefill ones
   int32_t deep;          // decode wavefronts keep two pages in flight
-  int32_t wide;          // a decode unit beside prefill units is the work of a workgroup
+  int32_t wide;          // wavefronts of the workgroup of a decode unit; 0: a wavefront each
   float scale_log2;      // softmax scale * log2(e)
   // Append launches only: this iteration's keys and values [tokens][hkv][128],
   // the leading workgroups that write the append records stored after the
@@ -1332,8 +1331,8 @@ __device__ __forceinline__ void decode_merge(const Args& a, const Slots sl, int 
 
 typedef short s16x4_t __attribute__((ext_vector_type(4)));
 
-// Decode unit of a wavefront (launches whose decode workgroups drain a queue
-// beside prefill units).  The unit's g heads are the columns of 16x16 matrix
+// Decode unit of a wavefront (in a launch whose decode workgroups drain a
+// queue).  The unit's g heads are the columns of 16x16 matrix
 // products (padded to 16 with zero queries): per page,
 // the scores are S^T = K Q^T (four v_mfma_f32_16x16x32_bf16 over the 128
 // dims) and the output advances by O^T += V^T P^T (eight
@@ -1594,11 +1593,11 @@ __device__ int decode_unit(const Args& a, const int32_t* it_g, char* wl, bool ta
   return ticket_v;
 }
 
-// Decode unit of a whole workgroup ("wide": launches without prefill units, and
-// those whose workgroups are all resident at once).  Wavefront w takes the unit's 32-key blocks (two
-// pages) w, w + NW, ..., so all finish together and the unit's partial results
-// meet in LDS; only units of 4096 keys and more are still merged across
-// workgroups.  Against one unit per wavefront (each of the four then merged
+// Decode unit of a whole workgroup ("wide").  Wavefront w takes the unit's
+// 32-key blocks (two pages) w, w + NW, ..., so all finish together and the unit's
+// partial results meet in LDS; only the parts of a range that the split policy
+// cut (it weighs parts from 192 keys on) are merged across workgroups, by the
+// last of them to finish.  Against one unit per wavefront (each of the four then merged
 // through device memory, 2-5 us) decode-only launches take: 4 sequences of
 // 64-256 keys 10.2 -> 5.7 us, one of 8000 keys (g = 4) 26.0 -> 13 us, 100 of
 // 300-2400 keys 115.8 -> 93 us, 256 of 2048-16384 keys (g = 8) 1567 -> 1490 us.
@@ -2101,7 +2100,7 @@ __global__ __launch_bounds__(THREADS, 2) void attention_wide_kernel(Args a) {
 }
 
 // Prefill units of any height beside wavefronts that drain a queue of decode
-// units.
+// units, and such wavefronts alone.
 template <int G, bool APP>
 __global__ __launch_bounds__(THREADS, 2) void attention_mixed_kernel(Args a) {
   __shared__ __attribute__((aligned(16))) char smem[LDS_BYTES];
@@ -2181,8 +2180,8 @@ __global__ __launch_bounds__(THREADS, 2) void attention_mixed_kernel(Args a) {
   }
 }
 
-// Launches without prefill units: one wide decode unit per workgroup, longest
-// first.
+// Launches without prefill units, but for many short units: one wide decode unit
+// per workgroup, longest first.
 template <int G, bool APP, int NW>
 __global__ __launch_bounds__(NW * 64, 2) void decode_kernel(Args a) {
   __shared__ __attribute__((aligned(16))) char smem[NW * WIDE_WAVE_LDS];
@@ -2218,15 +2217,9 @@ int compute_units() {
 
 template <int G, bool APP>
 hipError_t launch(const Args& a, int grid, hipStream_t stream) {
-  // Without prefill units: eight wavefronts to a unit while the units are few
-  // (a compute unit's workgroup then finishes its unit soonest: 512 units of
-  // 512-2048 keys, g = 2, 53.8 us against 58.1 with four), four, two workgroups
-  // to a compute unit, when they run in several rounds (one's prologue and sum
-  // then hide behind the other: 3656 units of the Qwen3-8B decoders 394 us
-  // against 406 with eight).
-  if (a.num_prefill == 0 && a.num_units > 4 * compute_units())
+  if (a.num_prefill == 0 && a.wide == 4)
     decode_kernel<G, APP, 4><<<a.num_units, 4 * 64, 0, stream>>>(a);
-  else if (a.num_prefill == 0)
+  else if (a.num_prefill == 0 && a.wide == 8)
     decode_kernel<G, APP, 8><<<a.num_units, 8 * 64, 0, stream>>>(a);
   else if (a.num_units == a.num_prefill)
     attention_wide_kernel<G, APP, false><<<grid, THREADS, 0, stream>>>(a);
@@ -2314,7 +2307,19 @@ int launch_mixed(const dlfp_dims* dims, const dlfp_meta* meta, const int32_t* d_
   const int cus = compute_units();
   const int decode_units = meta->num_units - meta->num_prefill_units;
   const int ahead = meta->num_prefill_units + a.app_wgs;
-  a.wide = dlfp::decode_by_workgroup(*meta, cus);
+  a.wide = dlfp::decode_by_workgroup(*meta, cus) ? 4 : 0;
+  // Without prefill units: eight wavefronts to a unit while the units are few
+  // and long (a compute unit's workgroup then finishes its unit soonest: 512
+  // units of 512-2048 keys, g = 2, 53.8 us against 58.1 with four), four, two
+  // workgroups to a compute unit, when they run in several rounds (one's
+  // prologue and sum then hide behind the other: 3656 units of the Qwen3-8B
+  // decoders 394 us against 406 with eight) or are short: a wavefront's part of
+  // up to 128 keys is a block at most either way (0.92x), and from one unit per
+  // compute unit on the larger workgroups take turns (up to 128 keys 0.65-0.75x,
+  // 256 0.8x, 512 0.88x, 1024 0.95x).
+  const bool several = meta->num_units > 4 * cus;
+  const bool shorter = meta->decode_split_tokens <= (meta->num_units > cus ? 1024 : 128);
+  if (a.wide && meta->num_prefill_units == 0 && !several && !shorter) a.wide = 8;
   const int decode_wgs = a.wide ? decode_units : std::min((decode_units + 3) / 4, 2 * cus);
   const int slots = ahead < 2 * cus ? std::max(2 * cus - ahead, 64) : 2 * cus;
   a.decode_waves = 4 * decode_wgs;

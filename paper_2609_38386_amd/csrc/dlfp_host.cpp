@@ -560,6 +560,10 @@ int dlfp_build_varlen_meta(const dlfp_dims* dims, const dlfp_tuning* tuning, int
                   : decode_split(pre_units < resident / 4
                                      ? std::max<int64_t>(resident / 4 - pre_units, 64)
                                      : resident / 4);
+    // Without prefill units the launch chooses its kernel by the longest unit:
+    // a split that cuts nothing is reported as that.
+    if (pre_units == 0 && max_kv > 0)
+      split_d = std::min<int64_t>(split_d, round_up(max_kv, DLFP_PAGE_SIZE));
   }
   // Build units: prefill (KV-head-major), then decode.  Capacity: every key
   // range is cut into at most ceil(range / split) parts, plus two tail pieces.

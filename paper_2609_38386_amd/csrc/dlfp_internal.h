@@ -22,20 +22,29 @@ inline int append_workgroups(int64_t records) {
   return wgs <= 16 ? (int)wgs : 0;
 }
 
-// Whether the decode units beside prefill units are each the work of a
-// workgroup, else of a wavefront.  When all workgroups fit the resident slots of
-// the device (two per compute unit) even with a workgroup to each unit, each
-// gets one: the launch is short and its end, where a wavefront's unit streams
-// alone at a quarter of what the compute unit could take, is most of it (g = 8,
-// 6 decoders of 250-2000 keys beside 47 new tokens: 18.9 -> 11.8 us; g = 4, 10
-// of 442-3536 beside 2: 21.7 -> 17.8 us).  Not for units of up to 128 keys, one
-// step of a workgroup, which the built-in split makes where the prefill share
-// sets the launch time (11 decoders of 38-304 keys beside 796 tokens over 858,
-// g = 2: 34.8 us, a workgroup each 35.3 us).  The two round their probabilities
+// Whether the decode units are each the work of a workgroup, else of a
+// wavefront.  Without prefill units: of a workgroup, but for units of at most 192
+// keys that are more than the resident workgroups (two per compute unit) and all
+// resident as wavefronts (eight): a workgroup is then mostly its start and its sum
+// (114 decoders of 29-58 keys, g = 2, 912 units: 9.0 us, a workgroup of four
+// wavefronts each 11.1; 116 of 16 keys: 9.0 and 12.3; 70 of 138 keys: 14.0 and
+// 17.8; from 200 keys on, at fewer units and in more than one round workgroups
+// are as fast or faster, 217 decoders of 23 keys, 3472 units, 29.0 and 48.6).
+// Beside prefill units: when all workgroups fit the resident slots of the device
+// even with a workgroup to each unit, each gets one: the launch is short and its
+// end, where a wavefront's unit streams alone at a quarter of what the compute
+// unit could take, is most of it (g = 8, 6 decoders of 250-2000 keys beside 47
+// new tokens: 18.9 -> 11.8 us; g = 4, 10 of 442-3536 beside 2: 21.7 -> 17.8 us).
+// Not for units of up to 128 keys, one step of a workgroup, which the built-in
+// split makes where the prefill share sets the launch time (11 decoders of 38-304
+// keys beside 796 tokens over 858, g = 2: 34.8 us, a workgroup each 35.3 us).  The two round their probabilities
 // against different reference maxima, so the rule takes only what the metadata
 // holds: the append records count also where another call writes them, and the
 // one- and two-launch forms give equal bits.
 inline bool decode_by_workgroup(const dlfp_meta& m, int64_t compute_units) {
+  if (m.num_prefill_units == 0)
+    return m.num_units <= 2 * compute_units || m.num_units > 8 * compute_units ||
+           m.decode_split_tokens > 192;
   return (int64_t)m.num_units + append_workgroups(m.num_append) <= 2 * compute_units &&
          m.decode_split_tokens > 128;
 }

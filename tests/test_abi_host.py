@@ -255,6 +255,17 @@ def test_meta_prefill_splits_leave_the_decode_share_its_slots(decoders, lo, hi):
     assert m.decode_split_tokens <= 2048, (m.num_prefill_units, m.decode_split_tokens)
 
 
+@pytest.mark.parametrize("longest,reported", [(1, 16), (100, 112), (128, 128), (129, 144),
+                                              (2000, 2000)])
+def test_meta_decode_only_reports_the_longest_unit(longest, reported):
+    """Without a prompt the launch chooses its kernel by the longest unit: many
+    decoders that no split cuts report their longest context, in whole pages."""
+    kv = [1 + (longest - 1) * i // 99 for i in range(100)]
+    bt = np.zeros((100, wl.pages_for(longest)), dtype=np.int32)
+    m = D.dlfp_build_varlen_meta(D.make_dims(16, 8), [1] * 100, kv, bt, 1)
+    assert m.num_units == 800 and m.decode_split_tokens == reported
+
+
 def test_meta_errors():
     dims = D.make_dims(16, 8)
     bt = np.array([[0, 1, 2]], dtype=np.int32)

@@ -212,3 +212,22 @@ def test_both_forms_take_the_same_decode_units(dev, g, decoders, ctx, chunk, spl
     got = _fused_vs_two_calls(dev, dims, seqs, _pool_for(seqs), 13, tuning=tuning,
                               label=f"edge g={g} {decoders} decoders, chunk {chunk}")
     _oracle_check(got, seqs, f"edge g={g} {decoders} decoders, chunk {chunk}")
+
+
+@pytest.mark.parametrize("g,decoders,lo,hi", [
+    (1, 16, 1, 128), (2, 16, 120, 200),      # up to one unit per compute unit: 4 and 8 wavefronts
+    (4, 33, 1, 1024), (8, 33, 1000, 1100),   # more: 4 up to 1024 keys, else 8
+    (2, 64, 1, 128), (8, 64, 100, 128),      # 512 units, a workgroup each
+    (1, 65, 1, 128), (2, 65, 192, 192), (4, 65, 1, 17), (8, 129, 1, 40),  # more: a wavefront each
+    (2, 65, 190, 193), (4, 129, 150, 300),   # longer ones: workgroups of four
+    (2, 256, 1, 30), (8, 257, 1, 30),        # 2048 units, a wavefront each; more: workgroups
+])
+def test_decode_only_units_by_number_and_length(dev, g, decoders, lo, hi):
+    """Decode-only launches of 8 KV heads on both sides of each line between the
+    kernels of a decode unit."""
+    shape = wl.AttnShape(8 * g, 8)
+    specs = [(1, lo + (hi - lo) * i // (decoders - 1)) for i in range(decoders)]
+    seqs = _seqs(shape, specs, seed=170 + decoders + g)
+    got = _fused_vs_two_calls(dev, D.make_dims(8 * g, 8), seqs, _pool_for(seqs), 17,
+                              label=f"decode only g={g}, {decoders} of {lo}-{hi} keys")
+    _oracle_check(got, seqs, f"decode only g={g}, {decoders} of {lo}-{hi} keys")
