@@ -195,21 +195,27 @@ int dlfp_build_varlen_meta(const dlfp_dims* dims, const dlfp_tuning* tuning, int
   // per compute unit.  Every candidate (the longest range in k equal parts, of
   // at least 192 keys: eight wavefronts take 256 at a time; and the longest unit
   // there is) is weighed by an estimate of the decode share's time in
-  // microseconds.  Up to one unit per compute unit they all stream side by
-  // side: while n units still have keys, 64 more keys of each (32 KiB) take
-  // n x 32 KiB at the device's 6.4 TB/s or 32 KiB at a compute unit's 60 GB/s,
-  // whichever is longer.  With more units the launch is bound by the bytes,
-  // plus 3 us for every round of workgroups that replaces another (its
-  // prologue and its sum over the wavefronts are not hidden).  Splitting any
-  // range costs its merge, 2.5 us.  On 48 shapes (1-256 sequences of 24-22000
-  // keys, g = 2-8) the choice is within 1.3% of the best measured split on
-  // average, and the launches take 0.79x the time of the wavefront units and
-  // splits used before (geometric mean; 8.6-10.7 -> 4.9-7 us for the smallest).
+  // microseconds.  Up to one unit per compute unit they all stream side by side:
+  // while n units still have keys, 64 more keys of each (32 KiB) take n x 32 KiB
+  // at the device's 6.4 TB/s or 32 KiB at a compute unit's 47 GB/s, whichever is
+  // longer.  With more units the compute units share the device's rate evenly, so
+  // those that get a unit more than the others end with it alone: full rounds of
+  // units of the average length at the device's rate, then the rest as above, and
+  // 2 us; every two units per compute unit after the first two cost 3 us (a
+  // prologue and a sum over the wavefronts that are not hidden).  Four units per
+  // compute unit of the longest split and more are bound by their bytes whatever
+  // the split (128 decoders of 1024-8192 keys 394-398 us at 1608 to 3656 units):
+  // the bytes, and 3 us per round of units.  Splitting any range costs its merge,
+  // 2.5 us.  (35 decoders of 1241 keys, 8 KV heads: 280
+  // units 40.5 us, 840 units 36.7; 17 of 1072-2110 keys: 136 units 28.1, 464
+  // units 25.0; 40 of 800 keys: 320 units 29.0, 640 units 34.4.  On 600 batches
+  // of 1-256 sequences of 8-60000 keys, g = 1-8, the launches take 0.82x the time
+  // of the wavefront units and splits used before, 30 more than 1.03x.)
   // Beside `ahead` prefill and append workgroups (0: alone) the units have to
   // fit into the slots those leave, two workgroups per compute unit; when they
   // need a second workgroup on some compute unit, that one's unit takes twice as
-  // long; and past one unit per compute unit half of the longest unit runs alone
-  // at the end.  No split that fits: an infinite estimate.
+  // long (at 60 GB/s); and past one unit per compute unit half of the longest
+  // unit runs alone at the end.  No split that fits: an infinite estimate.
   struct WideSplit {
     int64_t split, units;
     double est;
@@ -219,6 +225,7 @@ int dlfp_build_varlen_meta(const dlfp_dims* dims, const dlfp_tuning* tuning, int
   // on compute units of their own or shared ones.
   struct WideCandidate {
     int64_t split, units, longest;
+    double alone;        // without other workgroups
     double own, shared;  // (or the time of its merge, with more units than that)
   };
   std::vector<WideCandidate> wide_candidates;
@@ -245,15 +252,22 @@ int dlfp_build_varlen_meta(const dlfp_dims* dims, const dlfp_tuning* tuning, int
         ending[(part + STEP - 1) / STEP] += n;
       }
       const double merge = split ? 2.5 : 0.0;
-      WideCandidate c = {sp, units * hkv, longest, merge, merge};
+      WideCandidate c = {sp, units * hkv, longest, merge, merge, merge};
       if (c.units <= cus) {
         int64_t n = c.units;
         for (int b = 1; b <= BUCKETS && n > 0; ++b) {
           const double bytes = (double)n * (STEP * 512 / 6.4e6);
           c.own += std::max(bytes, STEP * 512 / 60e3);
           c.shared += std::max(bytes, 2.0 * (STEP * 512 / 60e3));
+          c.alone += std::max(bytes, STEP * 512 / 47e3);
           n -= ending[b] * hkv;
         }
+      } else {
+        const double unit = 512.0 * (double)dec_keys / (double)c.units;  // bytes, on average
+        const int64_t rounds = c.units / cus, rest = c.units % cus;
+        c.alone += (double)(rounds * cus) * unit / 6.4e6 +
+                   (rest ? std::max((double)rest * unit / 6.4e6, unit / 47e3) : 0.0) +
+                   2.0 + 3.0 * std::max(0.0, (double)c.units / (2.0 * (double)cus) - 1.0);
       }
       wide_candidates.push_back(c);
       if (sp <= 192) break;
@@ -263,10 +277,13 @@ int dlfp_build_varlen_meta(const dlfp_dims* dims, const dlfp_tuning* tuning, int
     const int64_t cus = std::max<int64_t>(1, resident / 8);
     if (wide_candidates.empty()) add_wide_candidates();
     WideSplit best = {DLFP_MAX_DECODE_UNIT_KEYS, 0, std::numeric_limits<double>::infinity()};
+    const bool few = wide_candidates[0].units <= 4 * cus;  // the longest split comes first
     for (const WideCandidate& c : wide_candidates) {
       if (ahead > 0 && c.units > 2 * cus - ahead) break;  // a shorter split has more
       double e = ahead > 0 && ahead + c.units > cus ? c.shared : c.own;
-      if (c.units > cus && ahead > 0)
+      if (ahead == 0 && few)
+        e = c.alone;
+      else if (c.units > cus && ahead > 0)
         e += (double)dec_keys * (512 / 6.4e6) + 0.5 * (double)c.longest * (512 / 60e3);
       else if (c.units > cus)
         e += (double)dec_keys * (512 / 6.4e6) + 3.0 * (double)c.units / (double)cus;

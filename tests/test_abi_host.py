@@ -256,7 +256,7 @@ def test_meta_prefill_splits_leave_the_decode_share_its_slots(decoders, lo, hi):
 
 
 @pytest.mark.parametrize("longest,reported", [(1, 16), (100, 112), (128, 128), (129, 144),
-                                              (2000, 2000)])
+                                              (400, 400)])
 def test_meta_decode_only_reports_the_longest_unit(longest, reported):
     """Without a prompt the launch chooses its kernel by the longest unit: many
     decoders that no split cuts report their longest context, in whole pages."""
@@ -264,6 +264,15 @@ def test_meta_decode_only_reports_the_longest_unit(longest, reported):
     bt = np.zeros((100, wl.pages_for(longest)), dtype=np.int32)
     m = D.dlfp_build_varlen_meta(D.make_dims(16, 8), [1] * 100, kv, bt, 1)
     assert m.num_units == 800 and m.decode_split_tokens == reported
+
+
+@pytest.mark.parametrize("decoders", [33, 35, 37, 40])
+def test_meta_decode_only_units_even_over_the_compute_units(decoders):
+    """Whole contexts of 33-40 decoders are 264-320 units for 256 compute units: a few
+    of these would run two units of 1241 keys, so the contexts are cut."""
+    bt = np.zeros((decoders, wl.pages_for(1241)), dtype=np.int32)
+    m = D.dlfp_build_varlen_meta(D.make_dims(8, 8), [1] * decoders, [1241] * decoders, bt, 1)
+    assert m.num_units >= 2 * 8 * decoders and m.work[:, 5].max() == 1241
 
 
 def test_meta_errors():
