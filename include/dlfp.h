@@ -357,7 +357,8 @@ int dlfp_workspace_error(const void* workspace, int32_t* host_error, hipStream_t
  * aligned); w: device bf16 [n][k] (one row per output feature, as a linear
  * layer's weight is stored), 16-byte aligned; out: device, row i at
  * out + i * ldo (ldo >= n, a multiple of 4), out_dtype 0 = bf16 (8-byte
- * aligned), 1 = fp32 (16-byte aligned).  fp32 accumulation.  n must be a
+ * aligned), 1 = fp32 (16-byte aligned).  fp32 accumulation, in an order that
+ * depends on m, n and k.  n must be a
  * multiple of 128 and k of 64 (DLFP_EUNSUPPORTED otherwise); m = 0 launches
  * nothing.  Errors: DLFP_EINVAL, DLFP_EUNSUPPORTED, DLFP_EHIP. */
 int dlfp_linear_bf16(int32_t m, int32_t n, int32_t k, const void* x, int32_t ldx, const void* w,

@@ -410,14 +410,17 @@ void launch_tile(const LinArgs& a, hipStream_t stream) {
 
 // Which kernel and tile: the one whose estimated time is lowest.  With
 // r = ceil(tiles / 256) rounds over the CUs and s = k / 64 K steps the estimate
-// is start + step s + (round + work s) r microseconds, fitted to 26 token
-// counts from 1 to 8192 times five (n, k) from 1024 x 1024 to 6144 x 1024 and
-// 1024 x 3072.  On that grid the choice is within 0.3% of the fastest variant
-// on average (4% at most), and against one 128 x 128 tile for every size, as
-// before, the launches take 0.44x of the time (geometric mean): n = k = 1024
+// is start + step s + (round + work s) r microseconds, fitted to 660 launches of
+// 1-8192 tokens times 24 (n, k), the Qwen3-0.6B, 8B and 32B projections among them
+// (relative errors; sizes where a variant takes over 1.8 times the best one's
+// time count little).  There the choice is within 0.4% of the fastest variant on
+// average, and against one 128 x 128 tile for every size, as before, the launches
+// take 0.42x of the time (geometric mean) and none takes longer: n = k = 1024
 // 11.0 -> 3.3 us at m = 32, 14.3 -> 6.3 us at m = 545, 28.2 -> 21.3 us at
 // m = 8192; n = 6144, k = 1024, m = 8192 141.5 -> 104.5 us; n = 1024, k = 3072,
-// m = 545 36.9 -> 12.1 us.  Small tiles win where the tiles are few, since
+// m = 545 36.9 -> 12.1 us; n = 5120, k = 8192, m = 4096 384 -> 353 us.  (A row's
+// sum over k runs in another order in another kernel, so its last bit can depend
+// on the number of rows.)  Small tiles win where the tiles are few, since
 // every CU then fills its LDS side by side; large ones where the tiles fill
 // the chip, since each operand byte then serves more products.
 struct Variant {
@@ -426,13 +429,13 @@ struct Variant {
   void (*launch)(const LinArgs&, hipStream_t);
 };
 constexpr Variant VARIANTS[] = {
-    {32, 32, 1.31f, -0.015f, 0.96f, 0.090f, launch_split<32, 32, 8, 2>},
-    {64, 32, 1.66f, -0.029f, 1.07f, 0.138f, launch_split<64, 32, 4, 3>},
-    {64, 64, 1.87f, -0.048f, 1.63f, 0.204f, launch_split<64, 64, 4, 2>},
-    {128, 64, 1.64f, 0.045f, 1.14f, 0.264f, launch_tile<128, 64, 2, 2, 3>},
-    {128, 128, 1.05f, -0.146f, 2.13f, 0.581f, launch_tile<128, 128, 2, 4, 4>},
-    {128, 256, 2.35f, -0.307f, 2.44f, 1.047f, launch_tile<128, 256, 2, 4, 3>},
-    {256, 256, 3.82f, -0.603f, 3.97f, 1.786f, launch_tile<256, 256, 2, 4, 2>},
+    {32, 32, 1.35f, -0.024f, 0.80f, 0.120f, launch_split<32, 32, 8, 2>},
+    {64, 32, 1.30f, -0.029f, 1.05f, 0.170f, launch_split<64, 32, 4, 3>},
+    {64, 64, 1.44f, -0.043f, 1.64f, 0.231f, launch_split<64, 64, 4, 2>},
+    {128, 64, 1.79f, 0.065f, 0.91f, 0.305f, launch_tile<128, 64, 2, 2, 3>},
+    {128, 128, 1.05f, -0.060f, 2.41f, 0.545f, launch_tile<128, 128, 2, 4, 4>},
+    {128, 256, 0.54f, -0.142f, 3.93f, 0.942f, launch_tile<128, 256, 2, 4, 3>},
+    {256, 256, -0.42f, -0.277f, 6.99f, 1.657f, launch_tile<256, 256, 2, 4, 2>},
 };
 constexpr int CUS = 256;
 // Row strides from here on take 64-bit offsets (255 rows of 2 bytes each fit

@@ -91,7 +91,7 @@ def test_linear_rejects_unsupported_shapes(dev):
 EDGES = [(1, 128, 64), (31, 256, 64), (256, 1024, 128), (257, 1024, 64), (33, 6144, 64),
          (65, 6144, 1024), (513, 1024, 1024), (513, 1024, 64), (129, 6144, 1024),
          (2049, 1024, 64), (321, 6144, 64), (641, 6144, 64), (2049, 2048, 192),
-         (1665, 6144, 64), (4097, 2048, 192), (673, 384, 192)]
+         (1665, 6144, 64), (4097, 2048, 192), (673, 384, 192), (161, 6144, 1024)]
 
 
 @pytest.mark.parametrize("m,n,k", EDGES)
