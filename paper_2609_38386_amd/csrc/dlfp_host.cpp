@@ -201,16 +201,16 @@ int dlfp_build_varlen_meta(const dlfp_dims* dims, const dlfp_tuning* tuning, int
   // longer.  With more units the compute units share the device's rate evenly, so
   // those that get a unit more than the others end with it alone: full rounds of
   // units of the average length at the device's rate, then the rest as above, and
-  // 2 us; every two units per compute unit after the first two cost 3 us (a
+  // 2.5 us; every two units per compute unit after the first two cost 3 us (a
   // prologue and a sum over the wavefronts that are not hidden).  Four units per
   // compute unit of the longest split and more are bound by their bytes whatever
   // the split (128 decoders of 1024-8192 keys 394-398 us at 1608 to 3656 units):
   // the bytes, and 3 us per round of units.  Splitting any range costs its merge,
-  // 2.5 us.  (35 decoders of 1241 keys, 8 KV heads: 280
-  // units 40.5 us, 840 units 36.7; 17 of 1072-2110 keys: 136 units 28.1, 464
-  // units 25.0; 40 of 800 keys: 320 units 29.0, 640 units 34.4.  On 600 batches
-  // of 1-256 sequences of 8-60000 keys, g = 1-8, the launches take 0.82x the time
-  // of the wavefront units and splits used before, 30 more than 1.03x.)
+  // 2.5 us.  (35 decoders of 1241 keys, 8 KV heads: 280 units 40.5 us, 840 units
+  // 36.7; 17 of 1072-2110 keys: 136 units 28.1, 464 units 25.0; 100 of 2000: 800
+  // units 147.4, 1600 units 141.8.  On 1000 batches of 1-256 sequences of 8-60000
+  // keys, g = 1-8, the launches take 0.824x the time of the wavefront units and
+  // splits used before, 61 of them more than 1.03x.)
   // Beside `ahead` prefill and append workgroups (0: alone) the units have to
   // fit into the slots those leave, two workgroups per compute unit; when they
   // need a second workgroup on some compute unit, that one's unit takes twice as
@@ -267,7 +267,7 @@ int dlfp_build_varlen_meta(const dlfp_dims* dims, const dlfp_tuning* tuning, int
         const int64_t rounds = c.units / cus, rest = c.units % cus;
         c.alone += (double)(rounds * cus) * unit / 6.4e6 +
                    (rest ? std::max((double)rest * unit / 6.4e6, unit / 47e3) : 0.0) +
-                   2.0 + 3.0 * std::max(0.0, (double)c.units / (2.0 * (double)cus) - 1.0);
+                   2.5 + 3.0 * std::max(0.0, (double)c.units / (2.0 * (double)cus) - 1.0);
       }
       wide_candidates.push_back(c);
       if (sp <= 192) break;
