@@ -257,6 +257,9 @@ __device__ __forceinline__ void wait_for_appends(const Args& a) {
 // writing back or invalidating whole L2 caches per unit.
 constexpr int CPOL_SC1 = 16;  // cache-policy bit: coherent at device scope
 
+// Loads past the group's slots return zero: a batch of a merge may reach past the
+// last split (a repeated split with a weight of zero would make an infinite
+// partial value a NaN).
 struct Slots {
   __amdgpu_buffer_rsrc_t r;
 };
@@ -453,7 +456,7 @@ __device__ __forceinline__ void prefill_merge(const Args& a, const Slots sl, int
       f32x4_t x[NB][PP];
 #pragma unroll
       for (int u = 0; u < NB; ++u) {
-        const int b = min(j + u, nsplits - 1) * slot_floats;
+        const int b = (j + u) * slot_floats;
         mj[u] = pload1(sl, b + rows * D + row);
         lj[u] = pload1(sl, b + rows * D + rows + row);
 #pragma unroll
@@ -1267,7 +1270,7 @@ __device__ __forceinline__ void decode_merge(const Args& a, const Slots sl, int 
   }
   for (int f0 = 0; f0 < nf; f0 += 64) {
     const int n = min(64, nf - f0);
-    const int fl = f0 + min(lane, n - 1);
+    const int fl = f0 + lane;
     const int lbase = (fl / G) * slot_floats + G * D + fl % G;
     const float mf = lane < n ? pload1(sl, lbase) : NEG_BIG;
     const float lf = pload1(sl, lbase + G);
@@ -1277,7 +1280,7 @@ __device__ __forceinline__ void decode_merge(const Args& a, const Slots sl, int 
       if (16 * q < n) {
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
-          const int fe = f0 + min(16 * q + e, n - 1);
+          const int fe = f0 + 16 * q + e;
           v[q][e] = pload2(sl, (fe / G) * slot_floats + (fe % G) * D + 2 * lane);
         }
       }
@@ -1931,14 +1934,15 @@ __device__ void decode_wide(const Args& a, const int32_t* it_g, char* smem, int*
       f32x4_t x[NB];
 #pragma unroll
       for (int u = 0; u < NB; ++u) {
-        const int b = min(j + u, nsplits - 1) * slot_floats;
+        const int b = (j + u) * slot_floats;
         mj[u] = pload1(sl, b + G * D + h);
         lj[u] = pload1(sl, b + G * D + G + h);
         x[u] = pload4(sl, b + h * D + 4 * q4);
       }
       float mn = M;
 #pragma unroll
-      for (int u = 0; u < NB; ++u) mn = fmaxf(mn, mj[u]);  // a repeated last split changes nothing
+      for (int u = 0; u < NB; ++u)
+        if (j + u < nsplits) mn = fmaxf(mn, mj[u]);
       const float rs = fexp2(M - mn);
       M = mn;
       L *= rs;

@@ -537,3 +537,58 @@ def test_kv_append_pages_anywhere(dev, case):
                      torch.from_numpy(slots).to(dev), pool.k, pool.v)
     got_k, got_v = pool.host_bits()
     assert np.array_equal(got_k, want_k) and np.array_equal(got_v, want_v)
+
+
+def _decode_batch(g, decoders, lo, hi, prompt):
+    shape = wl.AttnShape(8 * g, 8)
+    specs = [(1, lo + (hi - lo) * i // (decoders - 1)) for i in range(decoders)]
+    specs += [(prompt, prompt)] if prompt else []
+    return [wl.IterationSeq(wl.SeqStream(190 + g + decoders, wl.ROLE_DECODER if q == 1 else
+                                         wl.ROLE_PROMPT, i, shape, kv), q, kv)
+            for i, (q, kv) in enumerate(specs)]
+
+
+# A decode unit as a workgroup of eight, of four, and a wavefront; beside a prompt as a
+# workgroup and as a wavefront.
+DECODE_FORMS = [(1, 4, 300, 1500, 0), (2, 40, 17, 1100, 0), (4, 70, 1, 190, 0), (8, 70, 100, 192, 0),
+                (1, 70, 30, 180, 0), (2, 4, 64, 700, 40), (8, 80, 100, 400, 200),
+                (1, 80, 200, 600, 100)]
+
+
+@pytest.mark.parametrize("g,decoders,lo,hi,prompt", DECODE_FORMS)
+def test_decode_infinite_values(dev, ws, g, decoders, lo, hi, prompt):
+    """An infinite value of one key and dim makes that dim of its heads that infinity and
+    leaves every other output value as it was."""
+    seqs = _decode_batch(g, decoders, lo, hi, prompt)
+    pages = [wl.pages_for(s.kv_len) for s in seqs]
+    it = rt.Iteration(D.make_dims(8 * g, 8), seqs, sum(pages), 22, dev,
+                      fill_bits=rt.BF16_NAN_BITS)
+    print(f"g={g} {decoders} of {lo}-{hi}, prompt {prompt}", flush=True)
+    plain = it.run(ws, SCALE, torch.float32).clone()
+    want = plain.clone()
+    for i, s in enumerate(seqs[:decoders]):
+        key, head, dim, sign = (5 * i) % s.kv_len, i % 8, (11 * i) % 128, 1.0 - 2.0 * (i % 2)
+        t = key % 16
+        it.pool.v[int(it.block_table[i, key // 16]), head, dim,
+                  (t & 3) | ((t & 4) << 1) | ((t & 8) >> 1)] = sign * math.inf
+        want[i, head * g:(head + 1) * g, dim] = sign * math.inf
+    got = it.run(ws, SCALE, torch.float32, append=False)
+    assert torch.equal(got, want)
+
+
+@pytest.mark.parametrize("q,split", [(20, 256), (64, 512)])
+def test_prefill_merge_infinite_values(dev, ws, q, split):
+    """The same for the rows of a prompt's chunk over 12 and 6 splits of cached keys."""
+    g, kv = 2, 3072
+    seqs = [wl.IterationSeq(wl.SeqStream(196, wl.ROLE_PROMPT, 0, wl.AttnShape(8 * g, 8), kv), q, kv)]
+    it = rt.Iteration(D.make_dims(8 * g, 8), seqs, wl.pages_for(kv), 23, dev,
+                      fill_bits=rt.BF16_NAN_BITS, tuning=D.dlfp_tuning(0, split, 0, 0))
+    assert it.batch.meta.work[:, 8].max() == kv // split
+    plain = it.run(ws, SCALE, torch.float32).clone()
+    want = plain.clone()
+    for key, head, dim in ((0, 1, 9), (kv - q - 1, 6, 100)):  # in the first and the last split
+        t = key % 16
+        it.pool.v[int(it.block_table[0, key // 16]), head, dim,
+                  (t & 3) | ((t & 4) << 1) | ((t & 8) >> 1)] = math.inf
+        want[:, head * g:(head + 1) * g, dim] = math.inf
+    assert torch.equal(it.run(ws, SCALE, torch.float32, append=False), want)
