@@ -137,6 +137,33 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
   return __builtin_bit_cast(uint32_t, v);
 }
 
+// Decode products take a probability in two bf16 terms, at no matrix product
+// more: the columns that a unit's heads (at most 8 of 16) leave idle hold the same
+// heads again.  Columns 0-7 take a probability's upper half, cut off, and columns
+// 8-15 (`low`) the rest, which is then positive; at least the least normal number,
+// so that the product with an infinite value is that infinity in both.  A decode
+// row is then 3e-6 to 5e-6 off in the 2-norm where one rounded term left 1.1e-3 to
+// 1.6e-3.  (1000 decode-only batches 1.01x the time, those of up to 8 us 1.02x,
+// from 60 us on the same.)
+__device__ __forceinline__ uint32_t pack_term(float p0, float p1, bool low) {
+  typedef uint16_t u16x2_t __attribute__((ext_vector_type(2)));
+  const uint32_t b0 = __builtin_bit_cast(uint32_t, p0), b1 = __builtin_bit_cast(uint32_t, p1);
+  const uint32_t upper = __builtin_amdgcn_perm(b1, b0, 0x07060302u);
+  const uint32_t rest = pack_bf16(p0 - __builtin_bit_cast(float, b0 & 0xFFFF0000u),
+                                  p1 - __builtin_bit_cast(float, b1 & 0xFFFF0000u));
+  const u16x2_t least = {0x0080, 0x0080};
+  const u16x2_t kept = __builtin_elementwise_max(__builtin_bit_cast(u16x2_t, rest), least);
+  return low ? __builtin_bit_cast(uint32_t, kept) : upper;
+}
+// x plus the x of lane ^ 8 (rows of 16 lanes rotated by 8).  The sum is made
+// here and not where its lanes are used, which keeps it one instruction.
+__device__ __forceinline__ float sum_xor8(float x) {
+  float y = x + __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), 0x128,
+                                                                   0xF, 0xF, true));
+  asm volatile("" : "+v"(y));
+  return y;
+}
+
 __device__ __forceinline__ float fexp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
 __device__ __forceinline__ float shfl_xor(float x, int m) { return __shfl_xor(x, m); }
@@ -1336,11 +1363,11 @@ typedef short s16x4_t __attribute__((ext_vector_type(4)));
 
 // Decode unit of a wavefront (in a launch whose decode workgroups drain a
 // queue).  The unit's g heads are the columns of 16x16 matrix
-// products (padded to 16 with zero queries): per page,
+// products (twice, 8 columns apart, others with zero queries): per page,
 // the scores are S^T = K Q^T (four v_mfma_f32_16x16x32_bf16 over the 128
 // dims) and the output advances by O^T += V^T P^T (eight
 // v_mfma_f32_16x16x16_bf16 over the page's 16 keys), so the VALU only forms
-// the softmax.  Lane l owns head column l % 16 and accumulator rows
+// the softmax.  Lane l owns column l % 16 and accumulator rows
 // 4 (l / 16) .. + 3.  Row r of the K operand (and so of S^T) is token slot
 // vt_pos(r) of the page: a lane's four rows are then four consecutive
 // positions of a value-page row (the cache keeps V^T pages with slot t at
@@ -1365,7 +1392,7 @@ typedef short s16x4_t __attribute__((ext_vector_type(4)));
 // ends, so that its round trip overlaps the unit's last pages.
 template <int G, bool APP>
 __device__ int decode_unit(const Args& a, const int32_t* it_g, char* wl, bool take_ticket) {
-  static_assert(G >= 1 && G <= 16, "heads must fit the 16 columns");
+  static_assert(G >= 1 && G <= 8, "heads must fit half of the 16 columns");
   const int lane = threadIdx.x & 63;
   const int col = lane & 15, gq = lane >> 4;
   const record_ptr it = as_record(it_g);
@@ -1417,16 +1444,16 @@ __device__ int decode_unit(const Args& a, const int32_t* it_g, char* wl, bool ta
 
   // Prologue (one round trip after the work record): the first page, the
   // queries as the B operand (lane holds dims 32 kk + 8 (l / 16) .. + 8 of head
-  // column l % 16, zero past the unit's g heads), the unit's block ids and
+  // column l % 8, zero past the unit's g heads), the unit's block ids and
   // (append launches) the new token's key row and value pair.
   issue_block(first_blk, 0);
   bf16x8_t qb[4];
   {
-    const uint16_t* qp = a.q + ((int64_t)tok * a.hq + kh * G + min(col, G - 1)) * D + 8 * gq;
+    const uint16_t* qp = a.q + ((int64_t)tok * a.hq + kh * G + min(col & 7, G - 1)) * D + 8 * gq;
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk) {
       const u32x4_t v = *reinterpret_cast<const u32x4_t*>(qp + 32 * kk);
-      qb[kk] = __builtin_bit_cast(bf16x8_t, col < G ? v : u32x4_t{0u, 0u, 0u, 0u});
+      qb[kk] = __builtin_bit_cast(bf16x8_t, (col & 7) < G ? v : u32x4_t{0u, 0u, 0u, 0u});
     }
   }
   constexpr int PTV = DEC_PTAB / 64;
@@ -1535,14 +1562,15 @@ __device__ int decode_unit(const Args& a, const int32_t* it_g, char* wl, bool ta
 #pragma unroll
       for (int mb = 0; mb < 8; ++mb) o[mb] *= alpha;
     }
-    // P^T rounded to bf16: this lane's keys of its head column, the B operand.
+    // P^T: this lane's keys of its column, its term of each, the B operand.
     u32x2_t pk;
-    pk[0] = pack_bf16(fexp2(__builtin_fmaf(sc[0], c, -m_run)),
-                      fexp2(__builtin_fmaf(sc[1], c, -m_run)));
-    pk[1] = pack_bf16(fexp2(__builtin_fmaf(sc[2], c, -m_run)),
-                      fexp2(__builtin_fmaf(sc[3], c, -m_run)));
-    constexpr uint32_t ONES = 0x3F803F80u;  // two bf16 1.0
-    l_run = dot2(pk[1], ONES, dot2(pk[0], ONES, l_run));
+#pragma unroll
+    for (int w = 0; w < 2; ++w) {
+      const float e0 = fexp2(__builtin_fmaf(sc[2 * w], c, -m_run));
+      const float e1 = fexp2(__builtin_fmaf(sc[2 * w + 1], c, -m_run));
+      pk[w] = pack_term(e0, e1, col >= 8);
+      l_run = dot2(pk[w], 0x3F803F80u, l_run);  // two bf16 1.0
+    }
     const s16x4_t pb = __builtin_bit_cast(s16x4_t, pk);
     // O^T += V^T P^T, eight blocks of 16 dims.
 #pragma unroll
@@ -1559,8 +1587,13 @@ __device__ int decode_unit(const Args& a, const int32_t* it_g, char* wl, bool ta
     if (p + 1 < p_end) process(p + 1, 1);
   }
 
-  // Row sums: each lane group holds a quarter of the keys of its head.
-  const float l_tot = sum_xor32(sum_xor16(l_run));
+  // Row sums: each lane group holds a quarter of the keys of its head, the two
+  // columns of a head a term each.
+  const float l_tot = sum_xor8(sum_xor32(sum_xor16(l_run)));
+#pragma unroll
+  for (int mb = 0; mb < 8; ++mb)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) o[mb][i] = sum_xor8(o[mb][i]);
   // o[mb][i] = O[head col][16 mb + 4 gq + i]
   if (nsplits == 1) {
     if (col < G) {
@@ -1605,12 +1638,12 @@ __device__ int decode_unit(const Args& a, const int32_t* it_g, char* wl, bool ta
 // 64-256 keys 10.2 -> 5.7 us, one of 8000 keys (g = 4) 26.0 -> 13 us, 100 of
 // 300-2400 keys 115.8 -> 93 us, 256 of 2048-16384 keys (g = 8) 1567 -> 1490 us.
 //
-// The unit's g heads are the columns of 16x16 matrix products (padded to 16
-// with zero queries).  Per block the scores are S^T = K Q^T (two independent
+// The unit's g heads are the columns of 16x16 matrix products (twice, 8 columns
+// apart, others with zero queries).  Per block the scores are S^T = K Q^T (two independent
 // chains of four v_mfma_f32_16x16x32_bf16 over the 128 dims) and the output
 // advances by O^T += V^T P^T (eight of them over the 32 keys), half the
 // products, LDS reads and softmax steps per key of 16-key blocks.  Lane l owns
-// head column l % 16; its group q = l / 16 owns the eight keys at positions
+// column l % 16; its group q = l / 16 owns the eight keys at positions
 // 8 (q / 2) .. + 7 of page q % 2 (position p of a page holds token slot
 // vt_pos(p)).  Row r of the K operand of chain b is position
 // 8 (r / 8) + 4 b + r % 4 of page r / 4 % 2: the accumulator rows 4 q .. + 3 of
@@ -1629,7 +1662,7 @@ __device__ int decode_unit(const Args& a, const int32_t* it_g, char* wl, bool ta
 // read distinct banks.
 template <int G, bool APP, int NW>
 __device__ void decode_wide(const Args& a, const int32_t* it_g, char* smem, int* flag) {
-  static_assert(G >= 1 && G <= 16 && G * 32 <= NW * 64, "heads");
+  static_assert(G >= 1 && G <= 8 && G * 32 <= NW * 64, "heads");
   const int tid = threadIdx.x, wave = uniform(tid >> 6), lane = tid & 63;
   char* wl = smem + wave * WIDE_WAVE_LDS;
   const int col = lane & 15, gq = lane >> 4;
@@ -1694,18 +1727,18 @@ __device__ void decode_wide(const Args& a, const int32_t* it_g, char* smem, int*
     issue_v(p0, p1, npages > 1);
   }
   // With it go out the ids of the wavefront's pages, the queries as the B
-  // operand (lane holds dims 32 kk + 8 gq .. + 7 of its head column, zero past
+  // operand (lane holds dims 32 kk + 8 gq .. + 7 of head column l % 8, zero past
   // the g heads) and (append launches, the wavefront with the unit's last
   // block) the new token's key row (lanes 0-15, 16 bytes each) and its values of
   // dims 2 lane, 2 lane + 1.
   for (int x = lane; x < 2 * mine; x += 64) ptab[x] = bt[first_page + page_of(x >> 1, x & 1)];
   bf16x8_t qb[4];
   {
-    const uint16_t* qp = a.q + ((int64_t)tok * a.hq + kh * G + min(col, G - 1)) * D + 8 * gq;
+    const uint16_t* qp = a.q + ((int64_t)tok * a.hq + kh * G + min(col & 7, G - 1)) * D + 8 * gq;
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk) {
       const u32x4_t v = *reinterpret_cast<const u32x4_t*>(qp + 32 * kk);
-      qb[kk] = __builtin_bit_cast(bf16x8_t, col < G ? v : u32x4_t{0u, 0u, 0u, 0u});
+      qb[kk] = __builtin_bit_cast(bf16x8_t, (col & 7) < G ? v : u32x4_t{0u, 0u, 0u, 0u});
     }
   }
   const bool own_new =
@@ -1818,12 +1851,13 @@ __device__ void decode_wide(const Args& a, const int32_t* it_g, char* smem, int*
 #pragma unroll
       for (int mb = 0; mb < 8; ++mb) o[mb] *= alpha;
     }
-    // P^T rounded to bf16: this lane's keys of its head column, the B operand.
+    // P^T: this lane's keys of its column, its term of each, the B operand.
     u32x4_t pk;
 #pragma unroll
     for (int w = 0; w < 4; ++w) {
-      pk[w] = pack_bf16(fexp2(__builtin_fmaf(sc[2 * w], c, -m_run)),
-                        fexp2(__builtin_fmaf(sc[2 * w + 1], c, -m_run)));
+      const float e0 = fexp2(__builtin_fmaf(sc[2 * w], c, -m_run));
+      const float e1 = fexp2(__builtin_fmaf(sc[2 * w + 1], c, -m_run));
+      pk[w] = pack_term(e0, e1, col >= 8);
       l_run = dot2(pk[w], 0x3F803F80u, l_run);  // two bf16 1.0
     }
     const bf16x8_t pb = __builtin_bit_cast(bf16x8_t, pk);
@@ -1871,7 +1905,12 @@ __device__ void decode_wide(const Args& a, const int32_t* it_g, char* smem, int*
   // Each lane group holds a quarter of its head's keys.  Then the wavefronts'
   // results are added through LDS: quad (head, 4 mb + gq) holds dims
   // 16 mb + 4 gq .. + 3 of the head, thread (h, q4) sums quad q4 of head h.
-  const float l_tot = sum_xor32(sum_xor16(l_run));
+  // Before that the two columns of a head are added.
+  const float l_tot = sum_xor8(sum_xor32(sum_xor16(l_run)));
+#pragma unroll
+  for (int mb = 0; mb < 8; ++mb)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) o[mb][i] = sum_xor8(o[mb][i]);
   wait_memory_complete();
   __syncthreads();  // every wavefront is done with its slots
   f32x4_t* red = reinterpret_cast<f32x4_t*>(smem);

@@ -556,6 +556,22 @@ DECODE_FORMS = [(1, 4, 300, 1500, 0), (2, 40, 17, 1100, 0), (4, 70, 1, 190, 0), 
 
 
 @pytest.mark.parametrize("g,decoders,lo,hi,prompt", DECODE_FORMS)
+def test_decode_probabilities_keep_sixteen_bits(dev, ws, g, decoders, lo, hi, prompt):
+    """Decode rows in fp32: the error in the 2-norm stays under 2^-15 of the result (two bf16
+    terms leave less than 2^-16 of a probability; the fp32 scores and sums add about 1e-6)."""
+    seqs = _decode_batch(g, decoders, lo, hi, prompt)
+    pages = [wl.pages_for(s.kv_len) for s in seqs]
+    it = rt.Iteration(D.make_dims(8 * g, 8), seqs, sum(pages), 21, dev,
+                      fill_bits=rt.BF16_NAN_BITS)
+    print(f"g={g} {decoders} of {lo}-{hi}, prompt {prompt}", flush=True)
+    got = _to64(it.run(ws, SCALE, torch.float32))[:decoders]
+    want = np.concatenate(_oracle(seqs[:decoders]))
+    err = np.linalg.norm(got - want) / np.linalg.norm(want)
+    print(f"  error {err:.2e}", flush=True)
+    assert err <= 2.0 ** -15
+
+
+@pytest.mark.parametrize("g,decoders,lo,hi,prompt", DECODE_FORMS)
 def test_decode_infinite_values(dev, ws, g, decoders, lo, hi, prompt):
     """An infinite value of one key and dim makes that dim of its heads that infinity and
     leaves every other output value as it was."""
