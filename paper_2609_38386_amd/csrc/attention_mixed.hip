@@ -286,7 +286,7 @@ constexpr int CPOL_SC1 = 16;  // cache-policy bit: coherent at device scope
 
 // Loads past the group's slots return zero: a batch of a decode merge may reach
 // past the last split (a repeated split with a weight of zero would make an
-// infinite partial value a NaN).
+// infinite partial value a NaN, as the masked keys of a prefill tile make one).
 struct Slots {
   __amdgpu_buffer_rsrc_t r;
 };
@@ -460,9 +460,7 @@ __device__ __forceinline__ u32x4_t mask_elems(u32x4_t v, int limit, F key_of) {
 // layout), and the thread with index sub in its row takes pieces
 // sub + TPR i.  The loads of NB splits (pieces, maxima and sums) are issued
 // before any is consumed, so a batch costs about one memory round trip; NB is
-// chosen so that a batch holds about 136 registers; the splits past the last one
-// that it loads again are left out of the sum by a branch (zeros from past the
-// slots, as in the decode merges, cost a hundred spilled registers here).  Every load instruction
+// chosen so that a batch holds about 136 registers.  Every load instruction
 // of a wavefront reads whole contiguous runs of the partial layout.
 template <int G, int TPR>
 __device__ __forceinline__ void prefill_merge(const Args& a, const Slots sl, int slot_floats,
@@ -505,8 +503,7 @@ __device__ __forceinline__ void prefill_merge(const Args& a, const Slots sl, int
       for (int i = 0; i < PP; ++i) acc[i] *= rs;
 #pragma unroll
       for (int u = 0; u < NB; ++u) {
-        if (j + u >= nsplits) break;
-        const float w = fexp2(mj[u] - mn);
+        const float w = j + u < nsplits ? fexp2(mj[u] - mn) : 0.f;
         lsum += w * lj[u];
 #pragma unroll
         for (int i = 0; i < PP; ++i) acc[i] += w * x[u][i];

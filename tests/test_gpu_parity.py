@@ -590,21 +590,3 @@ def test_decode_infinite_values(dev, ws, g, decoders, lo, hi, prompt):
         want[i, head * g:(head + 1) * g, dim] = sign * math.inf
     got = it.run(ws, SCALE, torch.float32, append=False)
     assert torch.equal(got, want)
-
-
-@pytest.mark.parametrize("q,split", [(20, 256), (64, 512)])
-def test_prefill_merge_infinite_values(dev, ws, q, split):
-    """The same for the rows of a prompt's chunk over 12 and 6 splits of cached keys."""
-    g, kv = 2, 3072
-    seqs = [wl.IterationSeq(wl.SeqStream(196, wl.ROLE_PROMPT, 0, wl.AttnShape(8 * g, 8), kv), q, kv)]
-    it = rt.Iteration(D.make_dims(8 * g, 8), seqs, wl.pages_for(kv), 23, dev,
-                      fill_bits=rt.BF16_NAN_BITS, tuning=D.dlfp_tuning(0, split, 0, 0))
-    assert it.batch.meta.work[:, 8].max() == kv // split
-    plain = it.run(ws, SCALE, torch.float32).clone()
-    want = plain.clone()
-    for key, head, dim in ((0, 1, 9), (kv - q - 1, 6, 100)):  # in the first and the last split
-        t = key % 16
-        it.pool.v[int(it.block_table[0, key // 16]), head, dim,
-                  (t & 3) | ((t & 4) << 1) | ((t & 8) >> 1)] = math.inf
-        want[:, head * g:(head + 1) * g, dim] = math.inf
-    assert torch.equal(it.run(ws, SCALE, torch.float32, append=False), want)
