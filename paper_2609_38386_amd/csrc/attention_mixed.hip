@@ -137,14 +137,20 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
   return __builtin_bit_cast(uint32_t, v);
 }
 
-// Decode products take a probability in two bf16 terms, at no matrix product
-// more: the columns that a unit's heads (at most 8 of 16) leave idle hold the same
-// heads again.  Columns 0-7 take a probability's upper half, cut off, and columns
-// 8-15 (`low`) the rest, which is then positive; at least the least normal number,
-// so that the product with an infinite value is that infinity in both.  A decode
-// row is then 3e-6 to 5e-6 off in the 2-norm where one rounded term left 1.1e-3 to
-// 1.6e-3.  (1000 decode-only batches 1.01x the time, those of up to 8 us 1.02x,
-// from 60 us on the same.)
+// TWO: the decode products take a probability in two bf16 terms, at no matrix
+// product more: the columns that a unit's heads (at most 8 of 16) leave idle hold
+// the same heads again.  Columns 0-7 take a probability's upper half, cut off, and
+// columns 8-15 (`low`) the rest, which is then positive; at least the least normal
+// number, so that the product with an infinite value is that infinity in both.  A
+// row is then 3e-6 to 5e-6 off in the 2-norm where one rounded term leaves 1.1e-3
+// to 1.6e-3.  Launches of decode units alone take two terms (1000 batches 1.01x
+// the time, those of up to 8 us 1.02x, from 60 us on the same), and all units with
+// one query head per KV head; beside prefill tiles the instructions come out of
+// the tiles' time and power (Qwen3-8B, 128 decoders beside 1999 tokens: 1.006x).
+template <int G>
+constexpr bool two_terms(bool alone) {
+  return alone || G == 1;
+}
 __device__ __forceinline__ uint32_t pack_term(float p0, float p1, bool low) {
   typedef uint16_t u16x2_t __attribute__((ext_vector_type(2)));
   const uint32_t b0 = __builtin_bit_cast(uint32_t, p0), b1 = __builtin_bit_cast(uint32_t, p1);
@@ -1363,7 +1369,7 @@ typedef short s16x4_t __attribute__((ext_vector_type(4)));
 
 // Decode unit of a wavefront (in a launch whose decode workgroups drain a
 // queue).  The unit's g heads are the columns of 16x16 matrix
-// products (twice, 8 columns apart, others with zero queries): per page,
+// products (twice, 8 apart, with TWO; the others have zero queries): per page,
 // the scores are S^T = K Q^T (four v_mfma_f32_16x16x32_bf16 over the 128
 // dims) and the output advances by O^T += V^T P^T (eight
 // v_mfma_f32_16x16x16_bf16 over the page's 16 keys), so the VALU only forms
@@ -1390,11 +1396,11 @@ typedef short s16x4_t __attribute__((ext_vector_type(4)));
 // Returns the next queue ticket's pending value when asked to take one (see
 // the kernel's decode loop): the ticket is taken a few pages before the unit
 // ends, so that its round trip overlaps the unit's last pages.
-template <int G, bool APP>
+template <int G, bool APP, bool TWO>
 __device__ int decode_unit(const Args& a, const int32_t* it_g, char* wl, bool take_ticket) {
   static_assert(G >= 1 && G <= 8, "heads must fit half of the 16 columns");
   const int lane = threadIdx.x & 63;
-  const int col = lane & 15, gq = lane >> 4;
+  const int col = lane & 15, gq = lane >> 4, head = TWO ? col & 7 : col;
   const record_ptr it = as_record(it_g);
   const int s = it[DLFP_W_SEQ], kh = it[DLFP_W_KVHEAD];
   const int kb = it[DLFP_W_KVBEGIN], ke = it[DLFP_W_KVEND];
@@ -1444,16 +1450,16 @@ __device__ int decode_unit(const Args& a, const int32_t* it_g, char* wl, bool ta
 
   // Prologue (one round trip after the work record): the first page, the
   // queries as the B operand (lane holds dims 32 kk + 8 (l / 16) .. + 8 of head
-  // column l % 8, zero past the unit's g heads), the unit's block ids and
+  // column l % 16 (l % 8 with TWO), zero past the unit's g heads), the unit's block ids and
   // (append launches) the new token's key row and value pair.
   issue_block(first_blk, 0);
   bf16x8_t qb[4];
   {
-    const uint16_t* qp = a.q + ((int64_t)tok * a.hq + kh * G + min(col & 7, G - 1)) * D + 8 * gq;
+    const uint16_t* qp = a.q + ((int64_t)tok * a.hq + kh * G + min(head, G - 1)) * D + 8 * gq;
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk) {
       const u32x4_t v = *reinterpret_cast<const u32x4_t*>(qp + 32 * kk);
-      qb[kk] = __builtin_bit_cast(bf16x8_t, (col & 7) < G ? v : u32x4_t{0u, 0u, 0u, 0u});
+      qb[kk] = __builtin_bit_cast(bf16x8_t, head < G ? v : u32x4_t{0u, 0u, 0u, 0u});
     }
   }
   constexpr int PTV = DEC_PTAB / 64;
@@ -1568,7 +1574,7 @@ __device__ int decode_unit(const Args& a, const int32_t* it_g, char* wl, bool ta
     for (int w = 0; w < 2; ++w) {
       const float e0 = fexp2(__builtin_fmaf(sc[2 * w], c, -m_run));
       const float e1 = fexp2(__builtin_fmaf(sc[2 * w + 1], c, -m_run));
-      pk[w] = pack_term(e0, e1, col >= 8);
+      pk[w] = TWO ? pack_term(e0, e1, col >= 8) : pack_bf16(e0, e1);
       l_run = dot2(pk[w], 0x3F803F80u, l_run);  // two bf16 1.0
     }
     const s16x4_t pb = __builtin_bit_cast(s16x4_t, pk);
@@ -1587,13 +1593,16 @@ __device__ int decode_unit(const Args& a, const int32_t* it_g, char* wl, bool ta
     if (p + 1 < p_end) process(p + 1, 1);
   }
 
-  // Row sums: each lane group holds a quarter of the keys of its head, the two
-  // columns of a head a term each.
-  const float l_tot = sum_xor8(sum_xor32(sum_xor16(l_run)));
+  // Row sums: each lane group holds a quarter of the keys of its head (the two
+  // columns of a head a term each).
+  float l_tot = sum_xor32(sum_xor16(l_run));
+  if constexpr (TWO) {
+    l_tot = sum_xor8(l_tot);
 #pragma unroll
-  for (int mb = 0; mb < 8; ++mb)
+    for (int mb = 0; mb < 8; ++mb)
 #pragma unroll
-    for (int i = 0; i < 4; ++i) o[mb][i] = sum_xor8(o[mb][i]);
+      for (int i = 0; i < 4; ++i) o[mb][i] = sum_xor8(o[mb][i]);
+  }
   // o[mb][i] = O[head col][16 mb + 4 gq + i]
   if (nsplits == 1) {
     if (col < G) {
@@ -1638,8 +1647,8 @@ __device__ int decode_unit(const Args& a, const int32_t* it_g, char* wl, bool ta
 // 64-256 keys 10.2 -> 5.7 us, one of 8000 keys (g = 4) 26.0 -> 13 us, 100 of
 // 300-2400 keys 115.8 -> 93 us, 256 of 2048-16384 keys (g = 8) 1567 -> 1490 us.
 //
-// The unit's g heads are the columns of 16x16 matrix products (twice, 8 columns
-// apart, others with zero queries).  Per block the scores are S^T = K Q^T (two independent
+// The unit's g heads are the columns of 16x16 matrix products (twice, 8 apart,
+// with TWO; the others have zero queries).  Per block the scores are S^T = K Q^T (two independent
 // chains of four v_mfma_f32_16x16x32_bf16 over the 128 dims) and the output
 // advances by O^T += V^T P^T (eight of them over the 32 keys), half the
 // products, LDS reads and softmax steps per key of 16-key blocks.  Lane l owns
@@ -1660,12 +1669,12 @@ __device__ int decode_unit(const Args& a, const int32_t* it_g, char* wl, bool ta
 // page h keeps its 16-byte chunk x at position x ^ R ^ 8 h; V^T row d (32 bytes)
 // its two halves swapped when vt_swz(d): the lanes that LDS serves together
 // read distinct banks.
-template <int G, bool APP, int NW>
+template <int G, bool APP, int NW, bool TWO>
 __device__ void decode_wide(const Args& a, const int32_t* it_g, char* smem, int* flag) {
   static_assert(G >= 1 && G <= 8 && G * 32 <= NW * 64, "heads");
   const int tid = threadIdx.x, wave = uniform(tid >> 6), lane = tid & 63;
   char* wl = smem + wave * WIDE_WAVE_LDS;
-  const int col = lane & 15, gq = lane >> 4;
+  const int col = lane & 15, gq = lane >> 4, head = TWO ? col & 7 : col;
   const record_ptr it = as_record(it_g);
   const int s = it[DLFP_W_SEQ], kh = it[DLFP_W_KVHEAD];
   const int kb = it[DLFP_W_KVBEGIN], ke = it[DLFP_W_KVEND];
@@ -1727,18 +1736,18 @@ __device__ void decode_wide(const Args& a, const int32_t* it_g, char* smem, int*
     issue_v(p0, p1, npages > 1);
   }
   // With it go out the ids of the wavefront's pages, the queries as the B
-  // operand (lane holds dims 32 kk + 8 gq .. + 7 of head column l % 8, zero past
+  // operand (lane holds dims 32 kk + 8 gq .. + 7 of its head column, zero past
   // the g heads) and (append launches, the wavefront with the unit's last
   // block) the new token's key row (lanes 0-15, 16 bytes each) and its values of
   // dims 2 lane, 2 lane + 1.
   for (int x = lane; x < 2 * mine; x += 64) ptab[x] = bt[first_page + page_of(x >> 1, x & 1)];
   bf16x8_t qb[4];
   {
-    const uint16_t* qp = a.q + ((int64_t)tok * a.hq + kh * G + min(col & 7, G - 1)) * D + 8 * gq;
+    const uint16_t* qp = a.q + ((int64_t)tok * a.hq + kh * G + min(head, G - 1)) * D + 8 * gq;
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk) {
       const u32x4_t v = *reinterpret_cast<const u32x4_t*>(qp + 32 * kk);
-      qb[kk] = __builtin_bit_cast(bf16x8_t, (col & 7) < G ? v : u32x4_t{0u, 0u, 0u, 0u});
+      qb[kk] = __builtin_bit_cast(bf16x8_t, head < G ? v : u32x4_t{0u, 0u, 0u, 0u});
     }
   }
   const bool own_new =
@@ -1857,7 +1866,7 @@ __device__ void decode_wide(const Args& a, const int32_t* it_g, char* smem, int*
     for (int w = 0; w < 4; ++w) {
       const float e0 = fexp2(__builtin_fmaf(sc[2 * w], c, -m_run));
       const float e1 = fexp2(__builtin_fmaf(sc[2 * w + 1], c, -m_run));
-      pk[w] = pack_term(e0, e1, col >= 8);
+      pk[w] = TWO ? pack_term(e0, e1, col >= 8) : pack_bf16(e0, e1);
       l_run = dot2(pk[w], 0x3F803F80u, l_run);  // two bf16 1.0
     }
     const bf16x8_t pb = __builtin_bit_cast(bf16x8_t, pk);
@@ -1905,12 +1914,15 @@ __device__ void decode_wide(const Args& a, const int32_t* it_g, char* smem, int*
   // Each lane group holds a quarter of its head's keys.  Then the wavefronts'
   // results are added through LDS: quad (head, 4 mb + gq) holds dims
   // 16 mb + 4 gq .. + 3 of the head, thread (h, q4) sums quad q4 of head h.
-  // Before that the two columns of a head are added.
-  const float l_tot = sum_xor8(sum_xor32(sum_xor16(l_run)));
+  // Two terms: the columns of a head are added before.
+  float l_tot = sum_xor32(sum_xor16(l_run));
+  if constexpr (TWO) {
+    l_tot = sum_xor8(l_tot);
 #pragma unroll
-  for (int mb = 0; mb < 8; ++mb)
+    for (int mb = 0; mb < 8; ++mb)
 #pragma unroll
-    for (int i = 0; i < 4; ++i) o[mb][i] = sum_xor8(o[mb][i]);
+      for (int i = 0; i < 4; ++i) o[mb][i] = sum_xor8(o[mb][i]);
+  }
   wait_memory_complete();
   __syncthreads();  // every wavefront is done with its slots
   f32x4_t* red = reinterpret_cast<f32x4_t*>(smem);
@@ -2137,13 +2149,61 @@ __global__ __launch_bounds__(THREADS, 2) void attention_wide_kernel(Args a) {
     else
       prefill_unit<G, APP, DECODE>(a, rec, f, smem, &flag);
   } else if constexpr (DECODE) {
-    decode_wide<G, APP, 4>(a, a.work + (int64_t)(a.num_prefill - 1 - u) * DLFP_WORK_INTS, smem,
+    decode_wide<G, APP, 4, two_terms<G>(false)>(a, a.work + (int64_t)(a.num_prefill - 1 - u) * DLFP_WORK_INTS, smem,
                            &flag);
   }
 }
 
+// Decode workgroup d of a launch whose wavefronts drain a queue of decode units.
+template <int G, bool APP, bool TWO>
+__device__ __forceinline__ void decode_queue(const Args& a, int d, char* smem) {
+  // Decode wavefront w of decode workgroup d starts with unit 4 d + w when
+  // that is one of the first decode_static units (the workgroups resident
+  // from the start); the other units form a queue that wavefronts drain one
+  // ticket at a time as they finish, so none idles while units remain (a
+  // workgroup's slot frees only when all four of its wavefronts are done),
+  // and a workgroup that only becomes resident later takes tickets from the
+  // start instead of holding units back to the tail.  The last workgroup to
+  // finish resets the header words for the next launch.
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  char* wl = smem + wave * DEC_WAVE_LDS;
+  const int ndec = a.num_units - a.num_prefill;
+  const bool queue = ndec > a.decode_static;
+  auto ticket = [&]() {
+    int nt = 0;
+    if (lane == 0)
+      nt = a.decode_static + __hip_atomic_fetch_add(header_word(a.ws, HDR_TICKET), 1,
+                                                    __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return uniform(__shfl(nt, 0));
+  };
+  int t = d * 4 + wave;
+  if (queue && t >= a.decode_static) t = ticket();
+  while (t < ndec) {
+    // In queue mode the unit takes the next ticket itself near its end.
+    const int32_t* rec = a.work + (int64_t)(a.num_prefill + t) * DLFP_WORK_INTS;
+    int pending;
+    pending = decode_unit<G, APP, TWO>(a, rec, wl, queue);
+    wave_sync();
+    if (!queue) break;
+    t = a.decode_static + uniform(__shfl(pending, 0));
+  }
+  if (queue) {
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      const int d = __hip_atomic_fetch_add(header_word(a.ws, HDR_DONE), 1, __ATOMIC_RELAXED,
+                                           __HIP_MEMORY_SCOPE_AGENT);
+      if (d == a.decode_waves / 4 - 1) {
+        __hip_atomic_store(header_word(a.ws, HDR_TICKET), 0, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(header_word(a.ws, HDR_DONE), 0, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
+      }
+    }
+  }
+}
+
 // Prefill units of any height beside wavefronts that drain a queue of decode
-// units, and such wavefronts alone.
+// units.
 template <int G, bool APP>
 __global__ __launch_bounds__(THREADS, 2) void attention_mixed_kernel(Args a) {
   __shared__ __attribute__((aligned(16))) char smem[LDS_BYTES];
@@ -2158,69 +2218,20 @@ __global__ __launch_bounds__(THREADS, 2) void attention_mixed_kernel(Args a) {
     }
     b -= a.app_wgs;
   }
-  // Grid: `lead` prefill workgroups, `decode_lead` decode workgroups, the
-  // other prefill workgroups, the other decode workgroups.  The i-th prefill
-  // workgroup takes unit xcd_remap(i): decode_lead is a multiple of 8, so the
-  // i-th prefill workgroup runs on XCD i % 8 either way.
-  const int np = a.num_prefill, L = a.lead, DL = a.decode_lead;
-  int pi = -1, d = -1;
-  if (b < L)
-    pi = b;
-  else if (b < L + DL)
-    d = b - L;
-  else if (b < np + DL)
-    pi = b - DL;
-  else
-    d = b - np;
-  if (pi >= 0) {
-    const int u = xcd_remap(pi, np);
+  const int u = prefill_of(a, b);
+  if (u >= 0) {
     const int32_t* rec = a.work + (int64_t)u * DLFP_WORK_INTS;
     prefill_unit<G, APP, true>(a, rec, rec, smem, &flag);
   } else {
-    // Decode wavefront w of decode workgroup d starts with unit 4 d + w when
-    // that is one of the first decode_static units (the workgroups resident
-    // from the start); the other units form a queue that wavefronts drain one
-    // ticket at a time as they finish, so none idles while units remain (a
-    // workgroup's slot frees only when all four of its wavefronts are done),
-    // and a workgroup that only becomes resident later takes tickets from the
-    // start instead of holding units back to the tail.  The last workgroup to
-    // finish resets the header words for the next launch.
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    char* wl = smem + wave * DEC_WAVE_LDS;
-    const int ndec = a.num_units - a.num_prefill;
-    const bool queue = ndec > a.decode_static;
-    auto ticket = [&]() {
-      int nt = 0;
-      if (lane == 0)
-        nt = a.decode_static + __hip_atomic_fetch_add(header_word(a.ws, HDR_TICKET), 1,
-                                                      __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      return uniform(__shfl(nt, 0));
-    };
-    int t = d * 4 + wave;
-    if (queue && t >= a.decode_static) t = ticket();
-    while (t < ndec) {
-      // In queue mode the unit takes the next ticket itself near its end.
-      const int32_t* rec = a.work + (int64_t)(a.num_prefill + t) * DLFP_WORK_INTS;
-      int pending;
-      pending = decode_unit<G, APP>(a, rec, wl, queue);
-      wave_sync();
-      if (!queue) break;
-      t = a.decode_static + uniform(__shfl(pending, 0));
-    }
-    if (queue) {
-      __syncthreads();
-      if (threadIdx.x == 0) {
-        const int d = __hip_atomic_fetch_add(header_word(a.ws, HDR_DONE), 1, __ATOMIC_RELAXED,
-                                             __HIP_MEMORY_SCOPE_AGENT);
-        if (d == a.decode_waves / 4 - 1) {
-          __hip_atomic_store(header_word(a.ws, HDR_TICKET), 0, __ATOMIC_RELAXED,
-                             __HIP_MEMORY_SCOPE_AGENT);
-          __hip_atomic_store(header_word(a.ws, HDR_DONE), 0, __ATOMIC_RELAXED,
-                             __HIP_MEMORY_SCOPE_AGENT);
-        }
-      }
-    }
+    decode_queue<G, APP, two_terms<G>(false)>(a, -1 - u, smem);
   }
+}
+
+// Launches of many short decode units alone.
+template <int G, bool APP>
+__global__ __launch_bounds__(THREADS, 2) void decode_queue_kernel(Args a) {
+  __shared__ __attribute__((aligned(16))) char smem[4 * DEC_WAVE_LDS];
+  decode_queue<G, APP, two_terms<G>(true)>(a, blockIdx.x, smem);
 }
 
 // Launches without prefill units, but for many short units: one wide decode unit
@@ -2229,7 +2240,7 @@ template <int G, bool APP, int NW>
 __global__ __launch_bounds__(NW * 64, 2) void decode_kernel(Args a) {
   __shared__ __attribute__((aligned(16))) char smem[NW * WIDE_WAVE_LDS];
   __shared__ int flag;
-  decode_wide<G, APP, NW>(a, a.work + (int64_t)blockIdx.x * DLFP_WORK_INTS, smem, &flag);
+  decode_wide<G, APP, NW, two_terms<G>(true)>(a, a.work + (int64_t)blockIdx.x * DLFP_WORK_INTS, smem, &flag);
 }
 
 // Workspace of dlfp_append_attention_mixed_static: a fixed array in device
@@ -2264,6 +2275,8 @@ hipError_t launch(const Args& a, int grid, hipStream_t stream) {
     decode_kernel<G, APP, 4><<<a.num_units, 4 * 64, 0, stream>>>(a);
   else if (a.num_prefill == 0 && a.wide == 8)
     decode_kernel<G, APP, 8><<<a.num_units, 8 * 64, 0, stream>>>(a);
+  else if (a.num_prefill == 0)
+    decode_queue_kernel<G, APP><<<grid, THREADS, 0, stream>>>(a);
   else if (a.num_units == a.num_prefill)
     attention_wide_kernel<G, APP, false><<<grid, THREADS, 0, stream>>>(a);
   else if (a.wide)
