@@ -20,9 +20,9 @@ Every attention launch of the timed steps is bracketed with HIP events on the
 stream it runs on, which gives the per-launch durations behind the roofline
 figures.  Also reported in the same run: latency vs p_t, decode-only and
 prefill-only shares of the same kernel against the HBM and bf16 MFMA peaks,
-the Qwen3-0.6B sweep (28 layers, 28 pools) and the full Qwen3-8B sweep as
-other shapes, the closed-loop replay, and the CPU oracle's time on a bounded
-sample.
+and the CPU oracle's time on a bounded sample.  The Qwen3-0.6B sweep (28 layers,
+28 pools), the full Qwen3-8B sweep and the closed-loop replays run too: their
+summaries go to stderr, their results to the file that --details names.
 """
 from __future__ import annotations
 
@@ -61,6 +61,8 @@ def parse_args():
     ap.add_argument("--tuning", default=None,
                     help="work-list policy overrides for every sweep (the dlfp_tuning fields, "
                          "comma-separated; 0 = automatic)")
+    ap.add_argument("--details", default=None,
+                    help="file for the result line with the other shapes and the replays")
     ap.add_argument("--quiet", action="store_true")
     ap.add_argument("--two-launch", action="store_true",
                     help="append with dlfp_kv_append, then dlfp_attention_mixed (instead of "
@@ -1005,6 +1007,15 @@ def plot_latency(line, path):
     plt.close(fig)
 
 
+def report(line, details, path):
+    """The result line on stdout, short enough to be read whole from a log's end; what the
+    other shapes and the replays gave joins it in the file at `path`, if there is one."""
+    print(json.dumps(line), flush=True)
+    if path:
+        with open(path, "w") as fh:
+            fh.write(json.dumps({**line, **details}) + "\n")
+
+
 def main():
     args = parse_args()
     if args.plot_from:
@@ -1081,6 +1092,7 @@ def main():
         sys.exit(1)
     ms_per_step = r["wall"] * 1e3 / args.steps
     value = r["tokens"] / r["wall"]
+    details = {"other_shapes": extras, "replay": replay}
     line = {
         "metric": METRIC, "value": round(value, 1),
         "unit": "tok/s", "n_gpus": 1, "steps": args.steps, "warmup": args.warmup,
@@ -1102,13 +1114,11 @@ def main():
                        "decode_only_iter_ms": round(r["decode_only_iter_ms"], 4),
                        "rule": "Eq. 2, completion-timed (HIP events), quantum 128"},
         "workspace_error": errors,
-        "other_shapes": extras,
-        "replay": replay,
         "paper_context": "27.7% mean P99 ITL reduction, Qwen3-0.6B BF16, 1x A100 80GB (context only)",
     }
-    print(json.dumps(line), flush=True)
+    report(line, details, args.details)
     if args.plot:
-        plot_latency(line, args.plot)
+        plot_latency({**line, **details}, args.plot)
 
 
 if __name__ == "__main__":

@@ -1,5 +1,6 @@
 """Host logic of bench.py: the algorithmic work behind the roofline figures, the
 latency-vs-p_t figure, and the refusal of more than one GPU (no device needed)."""
+import json
 import os
 import subprocess
 import sys
@@ -54,6 +55,17 @@ def test_more_than_one_gpu_is_refused_before_any_device_call():
                        capture_output=True, text=True, timeout=120)
     assert r.returncode == 2
     assert "one GPU" in r.stderr
+
+
+def test_result_is_one_short_line_and_the_rest_a_file(tmp_path, capsys):
+    line = {"metric": "m", "value": 1.0}
+    details = {"other_shapes": {"a": 1}, "replay": {"b": [2] * 9000}}
+    path = tmp_path / "details.json"
+    bench.report(line, details, str(path))
+    bench.report(line, details, None)
+    out = capsys.readouterr().out.splitlines()
+    assert [json.loads(o) for o in out] == [line, line]
+    assert json.loads(path.read_text()) == {**line, **details}
 
 
 def test_source_hash_covers_the_kernel_and_its_policy():
