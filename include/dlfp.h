@@ -120,37 +120,37 @@ typedef struct {
  * unit a workgroup at 1024-key splits is latency-bound and takes tiles of 32
  * rows (32 / g tokens), whole or at the split of 4096, 2048, 1024, 512 or 256
  * keys that minimises an estimate of the launch time with its workgroups
- * within two per compute unit; otherwise, when the launch has a decode share,
- * the prefill takes the tallest tile of 128, 64 or 32 rows whose units, at the
- * shortest split of at least 1024 keys keeping them at most one per compute
- * unit, come within 1/16 of that count (when a lower tile would have more
- * units than that even unsplit, 128 rows at the shortest split giving at most
- * one and a half per compute unit; else 32 rows), unless an estimate of the
- * launch time puts another height and split of at most two units per compute
- * unit clearly ahead; a prefill share alone
- * takes 128-row tiles and the split (a multiple of 64 keys, at least 1024)
- * that minimises an estimate of the launch time.  Without a prefill share a
- * decode unit is the work of a workgroup (513 to 2048 units of at most 192 keys:
- * of a wavefront), and the decode split is the one in equal parts (of at least
- * 192 keys) that minimises an estimate of the launch time, the longest context
- * when that cuts nothing.  So it is beside a prefill share that leaves workgroup slots (two per
+ * within two per compute unit, unless they would far outlast the decode share;
+ * otherwise, when the launch has a decode share, the prefill takes the tallest
+ * tile of 128, 64 or 32 rows whose units, at the shortest split of at least
+ * 1024 keys keeping them at most one per compute unit, come within 1/16 of that
+ * count (when a lower tile would have more units than that even unsplit, 128
+ * rows at the shortest split giving at most one and a half per compute unit;
+ * else 32 rows), unless an estimate of the launch time puts another height and
+ * split of at most two units per compute unit clearly ahead that leaves a long
+ * decode share of one round its slots; a prefill share alone takes 128-row
+ * tiles and the split (a multiple of 64 keys, at least 1024) that minimises an
+ * estimate of the launch time.  Without a prefill share a decode unit is the
+ * work of a workgroup (513 to 2048 units of at most 192 keys: of a wavefront),
+ * and the decode split is the one in equal parts (of at least 192 keys) that
+ * minimises an estimate of the launch time, the longest context when that cuts
+ * nothing.  So it is beside a prefill share that leaves workgroup slots (two per
  * compute unit) for all of them, when the estimate is under that of wavefront
- * units (under 0.85 of it beside tiles of more than 32 rows); else a decode
- * unit beside a prefill share is a wavefront's (also when split into units of
- * up to 128 keys), and the split is either sqrt(256 W / F) keys for W decode keys over the F wavefronts of the
- * workgroup slots the prefill units leave (several queue rounds), or the
- * split that fits one round and best evens the decode workgroups over the
- * CUs, whichever an estimate of the launch time favours.  A range longer than
- * its split is cut into equal parts; the last of them is cut again into a half
- * and two quarters when the decode queue runs one to six rounds, or workgroup
- * units of 2048 keys and more one to eight.  Grid
- * layout: when a launch has decode
- * units and more prefill units than compute units, one prefill unit per
- * compute unit leads the grid, then the decode workgroups (up to one per
+ * units (under 0.85 of it beside tiles of more than 32 rows); else a decode unit
+ * beside a prefill share is a wavefront's (also when split into units of up to
+ * 128 keys), and the split is either sqrt(256 W / F) keys for W decode keys over
+ * the F wavefronts of the workgroup slots the prefill units leave (several queue
+ * rounds), or the split that fits one round and best evens the decode workgroups
+ * over the CUs, whichever an estimate of the launch time favours.  A range
+ * longer than its split is cut into equal parts; the last of them is cut again
+ * into a half and two quarters when the decode queue runs one to six rounds, or
+ * workgroup units of 2048 keys and more one to eight.  Grid layout: when a launch
+ * has decode units and more prefill units than compute units, one prefill unit
+ * per compute unit leads the grid, then the decode workgroups (up to one per
  * compute unit), then the other prefill units, so that the memory-bound decode
  * share runs beside the matrix-core-bound prefill share from the start instead
- * of after it.  Decode page depth of a wavefront's unit: one page in flight;
- * a launch without prefill units reports two. */
+ * of after it.  Decode page depth of a wavefront's unit: one page in flight
+ * beside a prefill share, two without one. */
 typedef struct {
   int32_t decode_split_tokens;   /* keys per decode unit; 0 = auto, else a multiple of 16,
                                     at most DLFP_MAX_DECODE_UNIT_KEYS */

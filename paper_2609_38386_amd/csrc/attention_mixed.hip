@@ -260,8 +260,11 @@ __device__ __forceinline__ void raise_error(float* ws, int code = 1) {
 // and the count is reached.  The poll is bounded all the same: after about
 // a second it raises error 2 and goes on.  A waiting unit counts itself on
 // a second word once its loop is done (it never polls again); the last one
-// zeroes both words for the next launch.  No page that holds a new token is
-// read before the wait, so no XCD's L2 holds an old copy of one.
+// zeroes both words for the next launch.  None of these units reads a page that
+// holds a new token before its wait, so it meets no old copy of one in its L2.
+// (Tiles of at most 32 rows and decode units do read such pages beside the
+// stores; they put the new tokens in from k_new and v_new, and no later launch
+// sees those copies: a launch begins with its L2s invalidated.)
 constexpr int APPEND_SPIN_LIMIT = 1 << 20;
 
 __device__ __forceinline__ void wait_for_appends(const Args& a) {
