@@ -475,7 +475,8 @@ int dlfp_build_varlen_meta(const dlfp_dims* dims, const dlfp_tuning* tuning, int
     // such splits are left out (8 decoders of 2741-14421 keys beside 8 prompts
     // of 100-400 tokens, g = 2: 440 units 138.1 us, 344 of them 90.5; a decode
     // share of many rounds gains from them: 148 decoders beside 4 prompts, 496
-    // units 87.9 us, 328 of them 120.3).
+    // units 87.9 us, 328 of them 120.3; with two units per compute unit no slot is
+    // left, and the decode share is cut for the whole device after them).
     int64_t least_units = 0;  // decode units at the longest split
     for (int s : decoders) least_units += hkv * ceil_div(kv_len[s], DLFP_MAX_DECODE_UNIT_KEYS);
     auto launch_est = [&](int64_t tt, int64_t sp, int64_t* units, double* prefill = nullptr) {
@@ -513,7 +514,7 @@ int dlfp_build_varlen_meta(const dlfp_dims* dims, const dlfp_tuning* tuning, int
         double pre = 0;
         const double e = launch_est(tt, sp, &n, &pre);
         if (n > 2 * target) break;
-        if (2 * n > 3 * target && wave_est > 0.5 * pre &&
+        if (2 * n > 3 * target && n < resident / 4 && wave_est > 0.5 * pre &&
             least_units <= 4 * std::max<int64_t>(2 * target - n, 64))
           continue;
         if (e < best) {

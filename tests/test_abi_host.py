@@ -275,6 +275,16 @@ def test_meta_decode_only_units_even_over_the_compute_units(decoders):
     assert m.num_units >= 2 * 8 * decoders and m.work[:, 5].max() == 1241
 
 
+def test_meta_prefill_splits_up_to_every_slot_stay_open():
+    """Two units per compute unit leave no slot at all: the decode share then follows the
+    prefill share on the whole device, in units cut for it."""
+    prompts = [(125, 260), (86, 951), (89, 0), (132, 5), (81, 8065), (75, 898)]
+    kv = [q + p for q, p in prompts] + [826 + 4377 * (2 * i + 1) // 30 for i in range(15)]
+    bt = np.zeros((len(kv), max(wl.pages_for(k) for k in kv)), dtype=np.int32)
+    m = D.dlfp_build_varlen_meta(D.make_dims(64, 8), [q for q, _ in prompts] + [1] * 15, kv, bt, 1)
+    assert m.num_prefill_units == 512 and m.decode_split_tokens <= 512
+
+
 def test_meta_errors():
     dims = D.make_dims(16, 8)
     bt = np.array([[0, 1, 2]], dtype=np.int32)
