@@ -214,8 +214,9 @@ int dlfp_build_varlen_meta(const dlfp_dims* dims, const dlfp_tuning* tuning, int
   // Beside `ahead` prefill and append workgroups (0: alone) the units have to
   // fit into the slots those leave, two workgroups per compute unit; when they
   // need a second workgroup on some compute unit, that one's unit takes twice as
-  // long (at 60 GB/s); and past one unit per compute unit half of the longest
-  // unit runs alone at the end.  No split that fits: an infinite estimate.
+  // long as at 60 GB/s; and past one unit per compute unit half of the longest
+  // unit runs alone at the end, at that rate.  No split that fits: an infinite
+  // estimate.
   struct WideSplit {
     int64_t split, units;
     double est;
@@ -257,11 +258,11 @@ int dlfp_build_varlen_meta(const dlfp_dims* dims, const dlfp_tuning* tuning, int
         int64_t n = c.units;
         for (int b = 1; b <= BUCKETS && n > 0; ++b) {
           const double bytes = (double)n * (STEP * 512 / 6.4e6);
-          c.own += std::max(bytes, STEP * 512 / 60e3);
+          c.own += std::max(bytes, STEP * 512 / 47e3);
           c.shared += std::max(bytes, 2.0 * (STEP * 512 / 60e3));
-          c.alone += std::max(bytes, STEP * 512 / 47e3);
           n -= ending[b] * hkv;
         }
+        c.alone = c.own;
       } else {
         const double unit = 512.0 * (double)dec_keys / (double)c.units;  // bytes, on average
         const int64_t rounds = c.units / cus, rest = c.units % cus;
